@@ -26,16 +26,19 @@ __device__ __forceinline__ Block4 philox10(uint32_t c0, uint32_t c1, uint32_t c2
     return {c0, c1, c2, c3};
 }
 
-// Whole-wave lane shifts through DPP (GFX9 wave_shr:1 / wave_shl:1).  Lanes
-// whose source lies outside the wave read 0 (bound_ctrl), which the callers
-// use as "no neighbour".  The move folds into the consuming VALU op.
+// Lane shifts through DPP over the whole wave (GFX9 wave_shr:1 / wave_shl:1) or
+// within its rows of 16 lanes (row_shr:1 / row_shl:1).  Lanes whose source lies
+// outside read 0 (bound_ctrl), which the callers use as "no neighbour".  The
+// move folds into the consuming VALU op.
+template <int WIDTH = 64>
 __device__ __forceinline__ float lane_from_left(float v) {   // lane l <- lane l-1
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+        0, __builtin_bit_cast(int, v), WIDTH == 64 ? 0x138 : 0x111, 0xF, 0xF, true));
 }
+template <int WIDTH = 64>
 __device__ __forceinline__ float lane_from_right(float v) {  // lane l <- lane l+1
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
+        0, __builtin_bit_cast(int, v), WIDTH == 64 ? 0x130 : 0x101, 0xF, 0xF, true));
 }
 
 __device__ __forceinline__ uint32_t lane_from_left_u32(uint32_t v) {
@@ -45,10 +48,17 @@ __device__ __forceinline__ uint32_t lane_from_right_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xF, 0xF, true);
 }
 
+// Sum over the wave's 64 lanes, in every lane: DPP adds within the rows of 16
+// lanes, then the rows' last lanes into the rows behind them (row_bcast:15 into
+// rows 1 and 3, row_bcast:31 into rows 2 and 3); the total ends in lane 63.
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 }  // namespace gga

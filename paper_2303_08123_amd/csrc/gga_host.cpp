@@ -98,7 +98,7 @@ int check_any_side_cfg(const gga_sim_cfg* c) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 
-int slab_plan(int L, int RR, int H, gga::SimArgs* a);
+int variant_plan(int v, int L, int substeps, gga::SimArgs* a);
 
 // gga_simulate's workspace for a side without a resident variant: the event
 // table (rows of GGA_KMAX fractions, so the size does not depend on K) and two
@@ -138,8 +138,9 @@ bool uses_teams(int v, int L, int substeps) {
     if (!g_use_teams.load() || v < 0 || !gga::variant_is_slab(v)) return false;
     gga::SimArgs a;
     std::memset(&a, 0, sizeof(a));
-    const int RR = gga::SIM_VARIANTS[v].rpt * gga::SIM_VARIANTS[v].nw;
-    return slab_plan(L, RR, substeps + 2, &a) > 0 && team_plan(&a, RR);
+    const gga::SimVariant& var = gga::SIM_VARIANTS[v];
+    const int RR = var.rpt * var.nw;
+    return variant_plan(v, L, substeps, &a) > 0 && team_plan(&a, RR);
 }
 
 // Instances whose state buffers a slab group keeps: all of them one step per
@@ -173,16 +174,71 @@ SimWs simulate_ws_layout(int L, int substeps, int32_t P, int32_t R) {
     return w;
 }
 
-// The instances at list positions 0 .. n-1 of a.inst_list as teams of slab
-// variant v, in cooperative launches of as many teams as the device holds at
-// once (at most `rows`, the instances the state buffers hold), each for its
-// instances' whole horizons.  a carries the slab plan with its export rows.
-hipError_t enqueue_teams(gga::SimArgs a, int v, int n, int rows, char* state, size_t state_bytes, int L,
-                         int32_t* flags, hipStream_t stream) {
+// The teams that slab variant v's launches hold at once (at most `rows`), and
+// its slab plan with the export rows in a.
+hipError_t team_launch(int v, int L, int rows, gga::SimArgs* a, int* teams, hipStream_t stream) {
+    const gga::SimVariant& var = gga::SIM_VARIANTS[v];
+    if (variant_plan(v, L, a->substeps, a) <= 0 || !team_plan(a, var.rpt * var.nw)) return hipErrorInvalidValue;
     int cap = 0;
-    hipError_t e = gga::launch_team_variant(v, a, 0, &cap, stream);
+    const hipError_t e = gga::launch_team_variant(v, *a, 0, &cap, stream);
+    *teams = std::min(8 * (cap / (8 * a->n_slabs)), rows);
+    return e;
+}
+
+// The longest of the teams' sums of steps when `teams` teams share n instances
+// as the kernel deals them (steps(k): those of list position k).
+template <class Steps>
+long long longest_team(int n, int teams, const Steps& steps) {
+    std::vector<long long> sum((size_t)teams, 0);
+    for (int k = 0; k < n; ++k) {
+        const int turn = k / teams, at = k % teams;
+        sum[(size_t)((turn & 1) ? teams - 1 - at : at)] += steps(k);
+    }
+    return n > 0 ? *std::max_element(sum.begin(), sum.end()) : 0;
+}
+
+// The slab variant that runs n instances of side L as teams in the least time.
+// Taller slabs are fewer per instance, so more instances run at once and less
+// halo is computed twice, but each step takes longer.  The side's measured
+// times decide: the longest team's steps times (substeps * sub + rest).  On
+// 256 x 256 with 10 sub-steps a step of up to 40 instances takes 29.3 us with 64
+// rows against 38.6 with 88 (six or four slabs each), and one of 256
+// instances 201 against 154 us.
+template <class Steps>
+hipError_t team_height(const gga::SimArgs& a, int v, int L, int n, int rows, const Steps& steps, int* best,
+                       hipStream_t stream) {
+    *best = v;
+    if (!gga::SIM_VARIANTS[v].heights) return hipSuccess;
+    double least = 0.0;
+    for (int u = 0; u < gga::N_SIM_VARIANTS; ++u) {
+        const gga::SimVariant& var = gga::SIM_VARIANTS[u];
+        if (var.L != L || !(var.sub > 0.0) || !uses_teams(u, L, a.substeps)) continue;
+        gga::SimArgs plan = a;
+        int teams = 0;
+        const hipError_t e = team_launch(u, L, rows, &plan, &teams, stream);
+        if (e != hipSuccess) return e;
+        if (teams < 1) continue;
+        const double us = (double)longest_team(n, teams, steps) * (a.substeps * var.sub + var.rest);
+        if (!(least > 0.0) || us < least) {
+            least = us;
+            *best = u;
+        }
+    }
+    return hipSuccess;
+}
+
+// The instances at list positions 0 .. n-1 of a.inst_list as teams of slab
+// variant v (or of the height that suits them), each for its whole horizon,
+// steps(k) for position k, max_steps the most: a cooperative launch of as many
+// teams as the device holds at once (at most `rows`, the instances the state
+// buffers hold), each taking list positions in turns.
+template <class Steps>
+hipError_t enqueue_teams(gga::SimArgs a, int v, int n, int rows, char* state, size_t state_bytes, int L,
+                         int32_t* flags, const Steps& steps, int max_steps, hipStream_t stream) {
+    int cap = 0, teams = 0;
+    hipError_t e = team_height(a, v, L, n, rows, steps, &v, stream);
+    if (e == hipSuccess) e = team_launch(v, L, rows, &a, &teams, stream);
     if (e != hipSuccess) return e;
-    const int teams = std::min(8 * (cap / (8 * a.n_slabs)), rows);
     if (teams < 1) return hipErrorInvalidConfiguration;
     const size_t fbytes = (size_t)L * L * 3 * sizeof(float) * (size_t)rows;
     a.fields = reinterpret_cast<float*>(state);
@@ -193,13 +249,19 @@ hipError_t enqueue_teams(gga::SimArgs a, int v, int n, int rows, char* state, si
     a.spin_limit = g_spin_limit.load();
     a.mode = 0;
     a.n0 = 0;
+    // a launch's step counts stay below 2^27, so that they leave room for the
+    // XCD; horizons beyond that run an instance per team and launch without it
+    const int turns = std::max(1, ((1 << 27) - 1) / std::max(1, max_steps));
+    a.flag_bits = max_steps < (1 << 27) ? 4 : 0;
     const int32_t* list = a.inst_list;
-    for (int k0 = 0; k0 < n && e == hipSuccess; k0 += teams) {
-        const int m = std::min(teams, n - k0);
+    for (int k0 = 0; k0 < n && e == hipSuccess;) {
         a.inst_list = list + k0;
-        a.n_active = m;
-        e = gga::launch_fill(flags, m * a.n_slabs, 0, stream);
-        if (e == hipSuccess) e = gga::launch_team_variant(v, a, gga::slab_blocks(m, a.n_slabs), &cap, stream);
+        a.n_active = std::min(teams, n - k0);
+        a.turns = std::min(turns, (n - k0 + a.n_active - 1) / a.n_active);
+        a.n_list = (int)std::min<long long>((long long)a.turns * a.n_active, n - k0);
+        k0 += a.n_list;
+        e = gga::launch_fill(flags, a.n_active * a.n_slabs, 0, stream);
+        if (e == hipSuccess) e = gga::launch_team_variant(v, a, gga::slab_blocks(a.n_active, a.n_slabs), &cap, stream);
     }
     return e;
 }
@@ -213,10 +275,7 @@ hipError_t enqueue_simulate_slabs(gga::SimArgs a, const gga_sim_cfg* cfg, int32_
                                   const SimWs& w, hipStream_t stream) {
     const int v = gga::variant_choice(cfg->L, false);
     if (v < 0 || !gga::variant_is_slab(v)) return hipErrorInvalidValue;
-    const gga::SimVariant& var = gga::SIM_VARIANTS[v];
-    const int RR = var.rpt * var.nw;
-    if (slab_plan(cfg->L, RR, cfg->substeps + 2, &a) <= 0) return hipErrorInvalidValue;
-    if (w.teams && !team_plan(&a, RR)) return hipErrorInvalidValue;
+    if (variant_plan(v, cfg->L, cfg->substeps, &a) <= 0) return hipErrorInvalidValue;
     int32_t* valid = reinterpret_cast<int32_t*>(ws + w.off_valid);
     int32_t* count = reinterpret_cast<int32_t*>(ws + w.off_count);
     int32_t* step = reinterpret_cast<int32_t*>(ws + w.off_step);
@@ -238,7 +297,8 @@ hipError_t enqueue_simulate_slabs(gga::SimArgs a, const gga_sim_cfg* cfg, int32_
         if (e == hipSuccess) e = gga::launch_slab_live(a, n, stream);
         if (e == hipSuccess)
             e = enqueue_teams(a, v, n, w.rows, ws + w.off_state, w.state_bytes, cfg->L,
-                              reinterpret_cast<int32_t*>(ws + w.off_flags), stream);
+                              reinterpret_cast<int32_t*>(ws + w.off_flags),
+                              [&](int) { return cfg->horizon; }, cfg->horizon, stream);
         return e;
     }
     const size_t fbytes = (size_t)cfg->L * cfg->L * 3 * sizeof(float) * (size_t)n;
@@ -1317,8 +1377,10 @@ int gga_sga_run(const gga_params* params, const gga_sim_cfg* cfg, const gga_ga_c
 namespace {
 
 // Slab rows for lattice side L, RR rows per workgroup and a halo of H rows:
-// the first and last slab own RR - H rows at the lattice edges, middle slabs
-// at most RR - 2H.  Returns the slab count (0: RR >= L, resident; -1: no plan).
+// the first and last slab own at most RR - H rows at the lattice edges, middle
+// slabs at most RR - 2H; the fewest slabs, their computed rows as even as they
+// go (so that each owns the rows its neighbours hold as halo, which teams
+// need).  Returns the slab count (0: RR >= L, resident; -1: no plan).
 int slab_plan(int L, int RR, int H, gga::SimArgs* a) {
     if (RR >= L) return 0;
     const int own_edge = RR - H;
@@ -1339,19 +1401,26 @@ int slab_plan(int L, int RR, int H, gga::SimArgs* a) {
     } else {
         const int mid = RR - 2 * H;
         if (mid < 1) return -1;
-        const int m = L - 2 * own_edge;
-        const int nm = (m + mid - 1) / mid;
-        add(0, 0, own_edge);
-        int at = own_edge;
-        for (int j = 0; j < nm; ++j) {
-            const int len = m / nm + (j < m % nm ? 1 : 0);
-            add(at - H, H, H + len);
-            at += len;
-        }
-        add(L - RR, H, RR);
+        const int nm = (L - 2 * own_edge + mid - 1) / mid;
+        // own rows of a middle slab: computed rows len + 2H as many as an edge
+        // slab's own + H, within what the edge slabs leave and mid
+        const int len = std::min(mid, std::max((L - 2 * own_edge + nm - 1) / nm, (L - 2 * H) / (nm + 2)));
+        const int first = (L - nm * len + 1) / 2, last = L - nm * len - first;
+        add(0, 0, first);
+        for (int j = 0; j < nm; ++j) add(first + j * len - H, H, H + len);
+        add(L - RR, RR - last, RR);
     }
     a->n_slabs = ns;
     return ns <= gga::MAX_SLABS ? ns : -1;
+}
+
+// The slab plan of variant v on side L with `substeps` sub-steps (0: resident
+// variant, -1: refused).  A variant accepts the sub-step counts for which slabs
+// of its `plan` rows have a plan, however tall its own slabs are.
+int variant_plan(int v, int L, int substeps, gga::SimArgs* a) {
+    const gga::SimVariant& var = gga::SIM_VARIANTS[v];
+    if (gga::variant_is_slab(v) && slab_plan(L, var.plan, substeps + 2, a) <= 0) return -1;
+    return slab_plan(L, var.rpt * var.nw, substeps + 2, a);
 }
 
 int side_ok(int L) { return gga::side_index(L) >= 0; }
@@ -1443,16 +1512,16 @@ hipError_t enqueue_uneven(const gga::SimArgs& base, const UnevenPlan& plan, char
             e = gga::launch_variant(g.variant, a, g.count, stream);
             continue;
         }
-        const gga::SimVariant& v = gga::SIM_VARIANTS[g.variant];
-        if (slab_plan(g.L, v.rpt * v.nw, a.substeps + 2, &a) <= 0) return hipErrorInvalidValue;
+        if (variant_plan(g.variant, g.L, a.substeps, &a) <= 0) return hipErrorInvalidValue;
         if (g.teams) {
-            if (!team_plan(&a, v.rpt * v.nw)) return hipErrorInvalidValue;
             a.nsteps = 0;                          // steps come from horizon[]
             e = gga::launch_slab_live(a, g.count, stream);
             if (e == hipSuccess)
                 e = enqueue_teams(a, g.variant, g.count, g.rows, ws + g.state_off,
                                   align256(state_bytes(g.L) * (size_t)g.rows), g.L,
-                                  reinterpret_cast<int32_t*>(ws + g.flags_off), stream);
+                                  reinterpret_cast<int32_t*>(ws + g.flags_off),
+                                  [&](int k) { return plan.host[plan.host.size() - P + plan.host[g.first + k] / R]; },
+                                  g.max_h, stream);
             continue;
         }
         const size_t sb = align256(state_bytes(g.L) * (size_t)g.count);
@@ -1599,8 +1668,7 @@ int gga_state_run_variant(const gga_params* params, const gga_sim_cfg* cfg, int3
     }
     if (nsteps < 1 || !fields2_d || !cells2_d || !ws_d || misaligned16(ws_d) || ws_bytes < gga_event_table_bytes(P, K))
         return GGA_E_ARG;
-    const gga::SimVariant& v = gga::SIM_VARIANTS[variant];
-    if (slab_plan(cfg->L, v.rpt * v.nw, cfg->substeps + 2, &a) <= 0) return GGA_E_UNSUPPORTED;
+    if (variant_plan(variant, cfg->L, cfg->substeps, &a) <= 0) return GGA_E_UNSUPPORTED;
     char* ws = static_cast<char*>(ws_d);
     int32_t* valid = reinterpret_cast<int32_t*>(ws);
     int32_t* count = valid + P;

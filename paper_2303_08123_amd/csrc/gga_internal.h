@@ -60,6 +60,8 @@ struct SimArgs {
     int32_t slab_exA[16], slab_exB[16];
     int32_t* team_flags;      // [n_active][n_slabs], zero before the launch
     int32_t spin_limit;
+    int32_t n_list, turns;    // list positions of the launch, and each team's share of them
+    int32_t flag_bits;        // low bits of a step count that name its publisher's XCD
 };
 constexpr int MAX_SLABS = 16;
 
@@ -68,37 +70,40 @@ constexpr int MAX_SLABS = 16;
 // CU 64 * cpl >= L.  Sides 64, 96, .., 256 (N_SIDES of them).
 struct SimVariant {
     int L, cpl, rpt, nw;
+    int plan;               // slab form: the sub-step counts accepted are those with a plan of slabs of this many rows
     const char* name;
+    double sub, rest;       // us of a team's sub-step and of the rest of its step, where team_height may take the variant
+    bool heights;           // teams: of the side's slabs, those that suit the number of instances (see team_height)
 };
 constexpr SimVariant SIM_VARIANTS[] = {
-    {64, 1, 4, 16, "L64 resident 4x1 x16 waves"},
-    {64, 1, 2, 16, "L64 slabs of 32 rows, 2x1 x16 waves"},
-    {128, 2, 8, 16, "L128 resident 8x2 x16 waves"},
-    {128, 2, 16, 8, "L128 resident 16x2 x8 waves"},
-    {128, 2, 4, 16, "L128 slabs of 64 rows, 4x2 x16 waves"},
-    {256, 4, 4, 16, "L256 slabs of 64 rows, 4x4 x16 waves"},
-    {256, 4, 8, 8, "L256 slabs of 64 rows, 8x4 x8 waves"},
-    {64, 1, 8, 8, "L64 resident 8x1 x8 waves"},
-    {64, 1, 16, 4, "L64 resident 16x1 x4 waves"},
+    {64, 1, 4, 16, 0, "L64 resident 4x1 x16 waves"},
+    {64, 1, 2, 16, 32, "L64 slabs of 32 rows, 2x1 x16 waves"},
+    {128, 2, 8, 16, 0, "L128 resident 8x2 x16 waves"},
+    {128, 2, 16, 8, 0, "L128 resident 16x2 x8 waves"},
+    {128, 2, 4, 16, 64, "L128 slabs of 64 rows, 4x2 x16 waves"},
+    {256, 4, 8, 8, 64, "L256 slabs of 64 rows, 8x4 x8 waves", 1.74, 14.0},
+    {256, 4, 11, 8, 64, "L256 slabs of 88 rows, 11x4 x8 waves", 2.4, 18.5, true},
+    {64, 1, 8, 8, 0, "L64 resident 8x1 x8 waves"},
+    {64, 1, 16, 4, 0, "L64 resident 16x1 x4 waves"},
     // sides below the row pitch 64 * cpl: the lanes past the lattice hold padding
-    {96, 2, 6, 16, "L96 resident 6x2 x16 waves (48 of 64 lanes)"},
-    {96, 2, 12, 8, "L96 resident 12x2 x8 waves (48 of 64 lanes)"},
-    {160, 4, 4, 16, "L160 slabs of 64 rows, 4x4 x16 waves (40 of 64 lanes)"},
-    {160, 4, 8, 8, "L160 slabs of 64 rows, 8x4 x8 waves (40 of 64 lanes)"},
-    {192, 4, 4, 16, "L192 slabs of 64 rows, 4x4 x16 waves (48 of 64 lanes)"},
-    {192, 4, 8, 8, "L192 slabs of 64 rows, 8x4 x8 waves (48 of 64 lanes)"},
-    {224, 4, 4, 16, "L224 slabs of 64 rows, 4x4 x16 waves (56 of 64 lanes)"},
-    {224, 4, 8, 8, "L224 slabs of 64 rows, 8x4 x8 waves (56 of 64 lanes)"},
-    {96, 2, 4, 16, "L96 slabs of 64 rows, 4x2 x16 waves (48 of 64 lanes)"},
+    {96, 2, 6, 16, 0, "L96 resident 6x2 x16 waves (48 of 64 lanes)"},
+    {96, 2, 12, 8, 0, "L96 resident 12x2 x8 waves (48 of 64 lanes)"},
+    {160, 4, 9, 8, 64, "L160 slabs of 72 rows, 9x4 x8 waves (40 of 64 lanes)"},
+    {160, 4, 8, 8, 64, "L160 slabs of 64 rows, 8x4 x8 waves (40 of 64 lanes)"},
+    {192, 4, 9, 8, 64, "L192 slabs of 72 rows, 9x4 x8 waves (48 of 64 lanes)"},
+    {192, 4, 8, 8, 64, "L192 slabs of 64 rows, 8x4 x8 waves (48 of 64 lanes)"},
+    {224, 4, 8, 8, 64, "L224 slabs of 64 rows, 8x4 x8 waves (56 of 64 lanes)", 1.85, 14.0},
+    {224, 4, 10, 8, 64, "L224 slabs of 80 rows, 10x4 x8 waves (56 of 64 lanes)", 2.65, 12.5, true},
+    {96, 2, 4, 16, 64, "L96 slabs of 64 rows, 4x2 x16 waves (48 of 64 lanes)"},
     // three columns per lane: 192 columns, no padding at 192, 160 of 192 at 160
-    {160, 3, 4, 16, "L160 slabs of 64 rows, 4x3 x16 waves (160 of 192 columns)"},
-    {160, 3, 8, 8, "L160 slabs of 64 rows, 8x3 x8 waves (160 of 192 columns)"},
-    {192, 3, 4, 16, "L192 slabs of 64 rows, 4x3 x16 waves"},
-    {192, 3, 8, 8, "L192 slabs of 64 rows, 8x3 x8 waves"},
-    // taller slabs (fewer of them per instance, so less halo recomputed)
-    {160, 3, 9, 8, "L160 slabs of 72 rows, 9x3 x8 waves (160 of 192 columns)"},
-    {192, 3, 9, 8, "L192 slabs of 72 rows, 9x3 x8 waves"},
-    {192, 3, 10, 8, "L192 slabs of 80 rows, 10x3 x8 waves"},
+    {160, 3, 12, 8, 64, "L160 slabs of 96 rows, 12x3 x8 waves (160 of 192 columns)", 2.05, 17.0},
+    {160, 3, 8, 8, 64, "L160 slabs of 64 rows, 8x3 x8 waves (160 of 192 columns)", 1.4, 15.2},
+    {192, 3, 14, 8, 64, "L192 slabs of 112 rows, 14x3 x8 waves", 2.35, 17.2},
+    {192, 3, 8, 8, 64, "L192 slabs of 64 rows, 8x3 x8 waves"},
+    // the tallest slabs (fewest of them per instance, so least halo recomputed)
+    {160, 3, 9, 8, 72, "L160 slabs of 72 rows, 9x3 x8 waves (160 of 192 columns)", 1.83, 14.3, true},
+    {192, 3, 9, 8, 72, "L192 slabs of 72 rows, 9x3 x8 waves", 1.52, 15.2},
+    {192, 3, 10, 8, 80, "L192 slabs of 80 rows, 10x3 x8 waves", 1.87, 14.5, true},
 };
 constexpr int N_SIM_VARIANTS = sizeof(SIM_VARIANTS) / sizeof(SIM_VARIANTS[0]);
 constexpr bool variant_is_slab(int v) { return SIM_VARIANTS[v].rpt * SIM_VARIANTS[v].nw < SIM_VARIANTS[v].L; }

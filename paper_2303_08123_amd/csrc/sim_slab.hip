@@ -117,18 +117,18 @@ hipError_t launch_slab_variant(int v, const SimArgs& a, int n_blocks, hipStream_
     switch (v) {
         case 1: return launch_slab<1, 2, 16>(a, n_blocks, stream);
         case 4: return launch_slab<2, 4, 16>(a, n_blocks, stream);
-        case 5: return launch_slab<4, 4, 16>(a, n_blocks, stream);
-        case 6: return launch_slab<4, 8, 8>(a, n_blocks, stream);
-        case 11: return launch_slab<4, 4, 16, 160>(a, n_blocks, stream);
+        case 5: return launch_slab<4, 8, 8>(a, n_blocks, stream);
+        case 6: return launch_slab<4, 11, 8>(a, n_blocks, stream);
+        case 11: return launch_slab<4, 9, 8, 160>(a, n_blocks, stream);
         case 12: return launch_slab<4, 8, 8, 160>(a, n_blocks, stream);
-        case 13: return launch_slab<4, 4, 16, 192>(a, n_blocks, stream);
+        case 13: return launch_slab<4, 9, 8, 192>(a, n_blocks, stream);
         case 14: return launch_slab<4, 8, 8, 192>(a, n_blocks, stream);
-        case 15: return launch_slab<4, 4, 16, 224>(a, n_blocks, stream);
-        case 16: return launch_slab<4, 8, 8, 224>(a, n_blocks, stream);
+        case 15: return launch_slab<4, 8, 8, 224>(a, n_blocks, stream);
+        case 16: return launch_slab<4, 10, 8, 224>(a, n_blocks, stream);
         case 17: return launch_slab<2, 4, 16, 96>(a, n_blocks, stream);
-        case 18: return launch_slab<3, 4, 16, 160>(a, n_blocks, stream);
+        case 18: return launch_slab<3, 12, 8, 160>(a, n_blocks, stream);
         case 19: return launch_slab<3, 8, 8, 160>(a, n_blocks, stream);
-        case 20: return launch_slab<3, 4, 16, 192>(a, n_blocks, stream);
+        case 20: return launch_slab<3, 14, 8, 192>(a, n_blocks, stream);
         case 21: return launch_slab<3, 8, 8, 192>(a, n_blocks, stream);
         case 22: return launch_slab<3, 9, 8, 160>(a, n_blocks, stream);
         case 23: return launch_slab<3, 9, 8, 192>(a, n_blocks, stream);
@@ -141,18 +141,18 @@ hipError_t launch_team_variant(int v, const SimArgs& a, int n_blocks, int* capac
     switch (v) {
         case 1: return launch_team<1, 2, 16>(a, n_blocks, capacity, stream);
         case 4: return launch_team<2, 4, 16>(a, n_blocks, capacity, stream);
-        case 5: return launch_team<4, 4, 16>(a, n_blocks, capacity, stream);
-        case 6: return launch_team<4, 8, 8>(a, n_blocks, capacity, stream);
-        case 11: return launch_team<4, 4, 16, 160>(a, n_blocks, capacity, stream);
+        case 5: return launch_team<4, 8, 8>(a, n_blocks, capacity, stream);
+        case 6: return launch_team<4, 11, 8>(a, n_blocks, capacity, stream);
+        case 11: return launch_team<4, 9, 8, 160>(a, n_blocks, capacity, stream);
         case 12: return launch_team<4, 8, 8, 160>(a, n_blocks, capacity, stream);
-        case 13: return launch_team<4, 4, 16, 192>(a, n_blocks, capacity, stream);
+        case 13: return launch_team<4, 9, 8, 192>(a, n_blocks, capacity, stream);
         case 14: return launch_team<4, 8, 8, 192>(a, n_blocks, capacity, stream);
-        case 15: return launch_team<4, 4, 16, 224>(a, n_blocks, capacity, stream);
-        case 16: return launch_team<4, 8, 8, 224>(a, n_blocks, capacity, stream);
+        case 15: return launch_team<4, 8, 8, 224>(a, n_blocks, capacity, stream);
+        case 16: return launch_team<4, 10, 8, 224>(a, n_blocks, capacity, stream);
         case 17: return launch_team<2, 4, 16, 96>(a, n_blocks, capacity, stream);
-        case 18: return launch_team<3, 4, 16, 160>(a, n_blocks, capacity, stream);
+        case 18: return launch_team<3, 12, 8, 160>(a, n_blocks, capacity, stream);
         case 19: return launch_team<3, 8, 8, 160>(a, n_blocks, capacity, stream);
-        case 20: return launch_team<3, 4, 16, 192>(a, n_blocks, capacity, stream);
+        case 20: return launch_team<3, 14, 8, 192>(a, n_blocks, capacity, stream);
         case 21: return launch_team<3, 8, 8, 192>(a, n_blocks, capacity, stream);
         case 22: return launch_team<3, 9, 8, 160>(a, n_blocks, capacity, stream);
         case 23: return launch_team<3, 9, 8, 192>(a, n_blocks, capacity, stream);

@@ -30,6 +30,10 @@ struct Q3Args {
     uint32_t* prop;                         // [inst][C][L][L] a proposer's target slot << 8 | its code
     int32_t* live;                          // [inst] or null
     int32_t* traj;                          // [inst][nsteps] or null
+    // set by q3_run: the fields' zero and the thresholds in field units, and the
+    // 32-bit threshold of the division probability
+    float zero[2], thOq, thGq, thOd, thGd, thHd;
+    uint32_t T_div;
 };
 // initial state of every instance into a.fields / a.cells
 hipError_t q3_init(const Q3Args& a, hipStream_t stream);

@@ -17,11 +17,13 @@
 // wave touch 64 consecutive sites.  An instance on a 128^2 lattice with 8
 // slots holds 256 KiB of words plus 192 KiB of fields, more than a compute
 // unit's LDS, so the state stays in device memory and a step is a chain of launches
-// over all instances at once: fraction, the FTCS sub-steps (fused in LDS
-// tiles, two field buffers), a fraction at the half hour, cell update,
+// over all instances at once: fraction, the FTCS sub-steps (in registers,
+// two field buffers), a fraction at the half hour, cell update,
 // resolution.  The per-site launches have one thread per site; an instance's
 // blocks are numbered so that they run on one XCD (blocks are dealt to the 8
 // XCDs in turn), keeping the rows a block shares with its neighbours in one L2.
+#include <cmath>
+
 #include "quasi3d.h"
 #include "sim_kernel.h"
 
@@ -51,6 +53,9 @@ __device__ __forceinline__ bool q3_place(const Q3Args& a, int& inst, int& site) 
     return true;
 }
 
+// the mask of EMPTY slots of a site without a cell
+__device__ __forceinline__ uint32_t q3_full(int C) { return 0xFFFFFFFFu >> (Q3_MAX_SLOTS - C); }
+
 __device__ __forceinline__ int sens_class(uint32_t w, const gga_params& P) {
     const int st = w & 3, age = (w >> 2) & 255;
     return st == QUIESC ? 3 : (age < P.class_age[0] ? 0 : (age < P.class_age[1] ? 1 : 2));
@@ -76,7 +81,7 @@ __device__ __forceinline__ void block_count(int cnt, int32_t* dst, int* s_part) 
     if (threadIdx.x == 0 && dst) {
         int t = 0;
         for (int w = 0; w < Q3_NT / 64; ++w) t += s_part[w];
-        atomicAdd(dst, t);
+        if (t) atomicAdd(dst, t);
     }
 }
 
@@ -164,6 +169,19 @@ __device__ __forceinline__ int find_fraction(const Q3Args& a, int p, int tau) {
     return (lo < cnt && st[lo] == tau) ? lo : -1;
 }
 
+// The same by a whole wave: each lane compares every 64th time.
+__device__ __forceinline__ int scan_fraction(const Q3Args& a, int p, int tau) {
+    const int32_t* st = a.ev_step + (size_t)p * a.K;
+    const int cnt = a.ev_count[p], lane = (int)threadIdx.x & 63;
+    for (int j0 = 0; j0 < a.K; j0 += 64) {
+        const int j = j0 + lane;
+        const int at = j < a.K ? st[j] : 0;       // beyond the count: not set, not looked at
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(j < cnt && at == tau);
+        if (hit) return j0 + __builtin_ctzll(hit);
+    }
+    return -1;
+}
+
 // Survival thresholds of fraction j of protocol p by class (and oxygen bin
 // with the oxygen effect) into s_thr; threads 0 .. 63 of the block.
 __device__ __forceinline__ void fraction_thresholds(const Q3Args& a, int p, int j, uint32_t (*s_thr)[GGA_OER_BINS]) {
@@ -219,132 +237,202 @@ __global__ void __launch_bounds__(Q3_NT) q3_fraction_kernel(Q3Args a, const floa
 
 // The FTCS sub-steps of the three fields in field units (boundary 0),
 // c' = lam ((N + S) + (W + E)) + (c (1 - 4 lam) + r), O and G clamped at the
-// units' zero, fused up to Q3_MAX_HALO per launch: a workgroup loads a
-// T x T tile of owned sites with a halo of h sites (the launch's sub-step
-// count) of the three fields and the reaction term into LDS, runs h sub-steps
-// there (sub-step k updates the region at least k + 1 sites inside the loaded
-// square, which its inputs fully determine), and stores the owned sites.
-// Sites outside the lattice hold 0, the boundary value in field units, and
-// every site's arithmetic is the 2D kernels' (so C = 1 reproduces them).
+// units' zero.  A workgroup holds a window of the lattice in registers, wave w
+// rows [w RPT, (w + 1) RPT) and lane l columns [l CPL, (l + 1) CPL), and runs
+// all of the launch's sub-steps there as the 2D kernel does (see sim_kernel.h:
+// forward and reverse pairs over RPT + 1 row slots, one barrier each, rows
+// exchanged with the neighbouring waves through LDS by state parity); every
+// site's arithmetic is the 2D kernel's (so C = 1 reproduces it).
+// A lattice of up to WIDE sites a side is one window, whatever the number of
+// sub-steps; rows and columns past it (PART) are held at 0, the boundary
+// value.  Larger lattices take windows that overlap by twice the launch's
+// sub-steps (Q3_MAX_HALO at most), each storing the sites that its inputs
+// fully determine.
+// Bound: 17 instructions per site and sub-step, and the state's round trip
+// (28 bytes per site).  512 instances of 128 x 128, 10 sub-steps: LDS tiles of
+// 64 x 64 owned sites (three LDS reads per site and field, two barriers per
+// sub-step, 1.7 times the sites) took 241 us, this 88.
 constexpr int Q3_MAX_HALO = 16;
-constexpr int Q3_BIG_TILE_MIN_L = 128;
-__host__ __device__ inline unsigned q3_tiles_per_inst(int L, int tile) {
-    const unsigned t = ((unsigned)L + tile - 1) / tile;
-    return t * t;
+constexpr int Q3_WIDE = 128, Q3_NARROW = 64;
+// windows of `side` sites per lattice dimension
+__host__ __device__ inline int q3_windows(int L, int side, int h) {
+    return L <= side ? 1 : (L - 2 * h + side - 2 * h - 1) / (side - 2 * h);
 }
-// rows a thread walks in the widest sub-step (w = EMAX - 2 columns, NT / w threads per column)
-constexpr int q3_run(int EMAX, int NT) { return (EMAX - 2 + NT / (EMAX - 2) - 1) / (NT / (EMAX - 2)); }
+struct __attribute__((packed, aligned(4))) Pair { float x, y; };
 
-// Tiles of Q3_TILE x Q3_TILE owned sites, EMAX the loaded side for the
-// launch's largest halo, NT threads.
-template <int Q3_TILE, int Q3_TILE_NT, int EMAX>
-__global__ void __launch_bounds__(Q3_TILE_NT) q3_diffuse_tile_kernel(Q3Args a, const float* src, float* dst, int h) {
-    __shared__ float s_f[3][EMAX * EMAX];
-    __shared__ float s_r[EMAX * EMAX];
+template <int CPL, int RPT, int NW, bool PART>
+__global__ void __launch_bounds__(64 * NW) q3_diffuse_kernel(Q3Args a, const float* src, float* dst, int count) {
+    constexpr int W = 64 * CPL, ODD = (6 * NW + 3) * W;
+    static_assert(RPT * NW == W && RPT >= 2 && CPL <= 2, "square windows");
+    __shared__ __attribute__((aligned(16))) float s_h[2 * ODD + 3 * W];
     const int L = a.L, L2 = L * L;
-    const int tpr = (L + Q3_TILE - 1) / Q3_TILE;
-    const unsigned tiles = q3_tiles_per_inst(L, Q3_TILE);
+    const int side = PART ? 1 : q3_windows(L, W, count);
+    const unsigned tiles = (unsigned)(side * side);
     const unsigned total = (unsigned)a.n_inst * tiles, per = (total + 7u) / 8u;
     const unsigned lb = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);     // XCD-grouped, as q3_place
     if (lb >= total) return;
     const int inst = (int)(lb / tiles), tile = (int)(lb - (unsigned)inst * tiles);
     if (!a.ev_valid[inst / a.R]) return;
-    const int y0 = (tile / tpr) * Q3_TILE - h, x0 = (tile % tpr) * Q3_TILE - h;   // lattice site of LDS (0, 0)
-    const int E = Q3_TILE + 2 * h;
-    const float* S = src + (size_t)inst * 3 * L2;
-    const float* Rg = a.react + (size_t)inst * L2;
-    // all of a thread's global loads are issued before its first LDS write
-    constexpr int LOADS = (EMAX * EMAX + Q3_TILE_NT - 1) / Q3_TILE_NT;
-    float ld[LOADS][4];
+    // first lattice row and column of the window, and what it stores
+    const int step = W - 2 * count, ty = tile / side, tx = tile - ty * side;
+    const int wy = PART ? 0 : min(ty * step, L - W), wx = PART ? 0 : min(tx * step, L - W);
+    const int oy0 = ty ? wy + count : 0, oy1 = ty + 1 < side ? min((ty + 1) * step, L - W) + count : L;
+    const int ox0 = tx ? wx + count : 0, ox1 = tx + 1 < side ? min((tx + 1) * step, L - W) + count : L;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    const int y0 = wy + wave * RPT, x0 = wx + lane * CPL;
+    const int rows = PART ? min(max(L - y0, 0), RPT) : RPT;              // the wave's rows of the lattice
+    float F[3][RPT + 1][CPL], Ro[RPT][CPL];
+    auto load = [&](const float* g, float (&v)[CPL]) {                   // one row's columns, 0 past the lattice
+        if constexpr (!PART && CPL == 2) {
+            const Pair q = *reinterpret_cast<const Pair*>(g);
+            v[0] = q.x;
+            v[CPL - 1] = q.y;
+        } else {
 #pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-        const int i = (int)threadIdx.x + j * Q3_TILE_NT;
-        const int ly = i / E, lx = i - ly * E;
-        const int gy = y0 + ly, gx = x0 + lx;
-        const bool in = i < E * E && gy >= 0 && gy < L && gx >= 0 && gx < L;
-        const size_t g = in ? (size_t)gy * L + gx : 0;
+            for (int c = 0; c < CPL; ++c) v[c] = x0 + c < L ? g[c] : 0.0f;
+        }
+    };
+    const float* S = src + (size_t)inst * 3 * L2 + (size_t)y0 * L + x0;
+    const float* Rg = a.react + (size_t)inst * L2 + (size_t)y0 * L + x0;
 #pragma unroll
-        for (int f = 0; f < 3; ++f) ld[j][f] = in ? S[(size_t)f * L2 + g] : 0.0f;
-        ld[j][3] = in ? Rg[g] : 0.0f;
-    }
+    for (int i = 0; i < RPT; ++i) {
 #pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-        const int i = (int)threadIdx.x + j * Q3_TILE_NT;
-        if (i < E * E) {
-            const int ly = i / E, o = ly * EMAX + (i - ly * E);
+        for (int c = 0; c < CPL; ++c) F[0][i][c] = F[1][i][c] = F[2][i][c] = Ro[i][c] = 0.0f;
+        if (!PART || i < rows) {
 #pragma unroll
-            for (int f = 0; f < 3; ++f) s_f[f][o] = ld[j][f];
-            s_r[o] = ld[j][3];
+            for (int f = 0; f < 3; ++f) load(S + (size_t)f * L2 + i * L, F[f][i]);
+            load(Rg + i * L, Ro[i]);
         }
     }
-    float lam[3], cen[3], lo[2];
+    float lam[3], cen[3];
 #pragma unroll
     for (int f = 0; f < 3; ++f) {
         lam[f] = a.prm.lambda[f];
         cen[f] = 1.0f - 4.0f * a.prm.lambda[f];
     }
-    lo[0] = to_field_units(a.prm, 0, 0.0);
-    lo[1] = to_field_units(a.prm, 1, 0.0);
+    const float lo[2] = {a.zero[0], a.zero[1]};
+    float* const hw = s_h + (3 + 6 * wave) * W + lane * CPL;
+    constexpr int TOP = 0, BOT = 3 * W, UP = -3 * W, DN = 6 * W, MID = RPT / 2;
+    auto put = [&](int at, int slot) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) hw[at + f * W + c] = F[f][slot][c];
+    };
+    auto get = [&](int at, float (&v)[3][CPL]) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) v[f][c] = hw[at + f * W + c];
+    };
+    auto row = [&](int k, int i, int to, const float (&edge)[3][CPL]) {
+        constexpr int NS = RPT + 1;
+        const int si = rot_slot<NS>(i, k);
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                const float above = (i == 0) ? edge[f][c] : F[f][rot_slot<NS>(i - 1, k)][c];
+                const float below = (i < RPT - 1) ? F[f][rot_slot<NS>(i + 1, k)][c] : edge[f][c];
+                const float west = (c > 0) ? F[f][si][c - 1] : lane_from_left(F[f][si][CPL - 1]);
+                const float east = (c < CPL - 1) ? F[f][si][c + 1] : lane_from_right(F[f][si][0]);
+                const float sum = (above + below) + (west + east);
+                F[f][to][c] = fmaf(lam[f], sum, fmaf(F[f][si][c], cen[f], Ro[i][c]));
+            }
+    };
+    // row i in slot `slot`: O and G clamped, sites past the lattice held at 0
+    auto bound = [&](int i, int slot) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                if (f < 2) asm("v_max_f32 %0, %0, %1" : "+v"(F[f][slot][c]) : "v"(lo[f]));
+                if (PART) F[f][slot][c] = i < rows && x0 + c < L ? F[f][slot][c] : 0.0f;
+            }
+    };
+    auto pin = [&] {                                     // sub-steps stay in order
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int j = 0; j <= RPT; ++j)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) asm volatile("" : "+v"(F[f][j][c]));
+    };
+    float hn[3][CPL], hd[3][CPL];
+    auto forward = [&] {
+        pin();
+        row(0, 0, RPT, hn);
+        bound(0, RPT);
+        put(TOP + ODD, RPT);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 1; i < MID; ++i) { row(0, i, i - 1, hn); bound(i, i - 1); }
+        __syncthreads();
+        get(DN, hd);
+        get(DN + ODD, hn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = MID; i < RPT; ++i) { row(0, i, i - 1, hd); bound(i, i - 1); }
+        put(BOT + ODD, RPT - 2);
+    };
+    // after a forward sub-step row i sits in slot i - 1 (row 0 in slot RPT)
+    auto reverse = [&] {
+        pin();
+        row(1, RPT - 1, RPT - 1, hn);
+        bound(RPT - 1, RPT - 1);
+        put(BOT, RPT - 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = RPT - 2; i >= RPT - MID; --i) { row(1, i, i, hn); bound(i, i); }
+        __syncthreads();
+        get(UP + ODD, hd);
+        get(UP, hn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = RPT - MID - 1; i >= 0; --i) { row(1, i, i, hd); bound(i, i); }
+        put(TOP, 0);
+    };
+    // ghost rows above and below the window, at both ends of each parity's area
+    for (int k = (int)threadIdx.x; k < 3 * 3 * W; k += 64 * NW) s_h[k / (3 * W) * (ODD - 3 * W) + k] = 0.0f;
+    put(TOP, 0);
+    put(BOT, RPT - 1);
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) F[f][RPT][c] = 0.0f;
     __syncthreads();
-    // Sub-step k computes the w x w square starting at (k + 1, k + 1).  Each
-    // thread takes one column of it and a run of at most RUN consecutive rows,
-    // walking down with the rows above and at the site in registers (three LDS
-    // reads per site and field: below, west, east); the new values wait in
-    // registers until every thread has read the old ones, so one LDS copy of
-    // the fields serves (more workgroups per CU).
-    constexpr int RUN = q3_run(EMAX, Q3_TILE_NT);    // ceil(w / (Q3_TILE_NT / w)) for w <= EMAX - 2
-    for (int k = 0; k < h; ++k) {
-        const int r0 = k + 1, w = E - 2 * (k + 1);
-        const int nseg = Q3_TILE_NT / w, rows = (w + nseg - 1) / nseg;
-        const int col = (int)threadIdx.x % w, seg = (int)threadIdx.x / w;
-        const int ly0 = r0 + seg * rows, ly1 = min(ly0 + rows, r0 + w);
-        const bool act = seg < nseg && ly0 < ly1;
-        const int lx = r0 + col, gx = x0 + lx;
-        float nv[RUN][3];
-        if (act) {
-            const bool col_in = gx >= 0 && gx < L;
-            int o = ly0 * EMAX + lx;
-            float up[3] = {s_f[0][o - EMAX], s_f[1][o - EMAX], s_f[2][o - EMAX]};
-            float mid[3] = {s_f[0][o], s_f[1][o], s_f[2][o]};
+    get(UP, hn);
+    int left = count;
+#pragma nounroll
+    for (; left >= 2; left -= 2) {
+        forward();
+        reverse();
+    }
+    if (left) {                                          // a last single one, its rows moved back by a copy
+        forward();
 #pragma unroll
-            for (int q = 0; q < RUN; ++q, o += EMAX) {
-                if (ly0 + q < ly1) {
-                    const int gy = y0 + ly0 + q;
-                    const bool in = col_in && gy >= 0 && gy < L;
-                    const float R = s_r[o];
+        for (int f = 0; f < 3; ++f)
 #pragma unroll
-                    for (int f = 0; f < 3; ++f) {
-                        const float below = s_f[f][o + EMAX];
-                        const float sum = (up[f] + below) + (s_f[f][o - 1] + s_f[f][o + 1]);
-                        float v = fmaf(lam[f], sum, fmaf(mid[f], cen[f], R));
-                        if (f < 2) v = fmaxf(v, lo[f]);
-                        nv[q][f] = in ? v : 0.0f;
-                        up[f] = mid[f];
-                        mid[f] = below;
-                    }
+            for (int i = RPT - 1; i >= 0; --i)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) F[f][i][c] = F[f][i ? i - 1 : RPT][c];
+    }
+    float* D = dst + (size_t)inst * 3 * L2 + (size_t)y0 * L + x0;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+        if (y0 + i >= oy0 && y0 + i < oy1) {
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+                float* d = D + (size_t)f * L2 + i * L;
+                if (!PART && CPL == 2 && x0 >= ox0 && x0 + 1 < ox1) {
+                    *reinterpret_cast<Pair*>(d) = Pair{F[f][i][0], F[f][i][CPL - 1]};
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c)
+                        if (x0 + c >= ox0 && x0 + c < ox1) d[c] = F[f][i][c];
                 }
             }
         }
-        __syncthreads();
-        if (act) {
-#pragma unroll
-            for (int q = 0; q < RUN; ++q)
-                if (ly0 + q < ly1)
-#pragma unroll
-                    for (int f = 0; f < 3; ++f) s_f[f][(ly0 + q) * EMAX + lx] = nv[q][f];
-        }
-        __syncthreads();
-    }
-    float* D = dst + (size_t)inst * 3 * L2;
-    for (int i = threadIdx.x; i < Q3_TILE * Q3_TILE; i += Q3_TILE_NT) {
-        const int qy = i / Q3_TILE;
-        const int ly = h + qy, lx = h + (i - qy * Q3_TILE);
-        const int gy = y0 + ly, gx = x0 + lx;
-        if (gy >= L || gx >= L) continue;
-        const size_t g = (size_t)gy * L + gx;
-#pragma unroll
-        for (int f = 0; f < 3; ++f) D[(size_t)f * L2 + g] = s_f[f][ly * EMAX + lx];
-    }
 }
 
 // Cell update from the snapshot (cells, after the fractions; its EMPTY slots
@@ -355,46 +443,44 @@ __global__ void __launch_bounds__(Q3_TILE_NT) q3_diffuse_tile_kernel(Q3Args a, c
 // slots targeted in the previous step are cleared (those slots now hold cells,
 // so no proposal of this step reaches them) and that mask is zeroed for the
 // next step.
+// Sites without a cell, most of a lattice, need their masks only: 512 instances
+// of 128 x 128 x 8 (seeded, 5 days) took 113 us with every site's words and
+// fields read, 47 now.  (With four sites per thread and a quarter of the blocks 84:
+// the sites of the tumour then wait for one another.)
 __global__ void __launch_bounds__(Q3_NT) q3_update_kernel(Q3Args a, const float* F, int n) {
     int inst, site;
     if (!q3_place(a, inst, site)) return;
     const int p = inst / a.R, r = inst - p * a.R;
     if (!a.ev_valid[p]) return;
-    __shared__ CellConst s_k;
     const gga_params& P = a.prm;
-    if (threadIdx.x == 0) {
-        s_k.thOq = to_field_units(P, 0, P.theta_O_quiesce);
-        s_k.thGq = to_field_units(P, 1, P.theta_G_quiesce);
-        s_k.thOd = to_field_units(P, 0, P.theta_O_death);
-        s_k.thGd = to_field_units(P, 1, P.theta_G_death);
-        s_k.thHd = to_field_units(P, 2, P.theta_H_death);
-        s_k.T_div = (P.P_div >= 1.0) ? 0xFFFFFFFFu : (uint32_t)floor(P.P_div * 4294967296.0);
-    }
-    __syncthreads();
     const int L = a.L, L2 = L * L, C = a.C;
     if (site >= L2) return;
     const size_t plane = (size_t)a.n_inst * L2;
     uint32_t* t_now = a.tmask + (n & 1) * plane + (size_t)inst * L2;
     uint32_t* t_prev = a.tmask + ((n + 1) & 1) * plane + (size_t)inst * L2;
     unsigned long long* ky = a.keys + (size_t)inst * C * L2;
-    for (uint32_t tp = t_prev[site]; tp; tp &= tp - 1) ky[(size_t)__builtin_ctz(tp) * L2 + site] = NONE_KEY64;
-    t_prev[site] = 0;
+    const uint32_t* em = a.emask + (size_t)inst * L2;
+    const uint32_t own_empty = em[site];
+    if (uint32_t tp = t_prev[site]) {
+        for (; tp; tp &= tp - 1) ky[(size_t)__builtin_ctz(tp) * L2 + site] = NONE_KEY64;
+        t_prev[site] = 0;
+    }
+    if (own_empty == q3_full(C)) return;        // no cell: the resolution knows it by the same mask
 
     const float* Fi = F + (size_t)inst * 3 * L2;
     const float O = Fi[site], Gl = Fi[L2 + site], H = Fi[2 * L2 + site];
     // H's units have a negative scale, so H > theta reads H^ < theta^
-    const bool nec = (Gl < s_k.thGd) || (O < s_k.thOd) || (H < s_k.thHd);
-    const bool starv = (O < s_k.thOq) || (Gl < s_k.thGq);
-    const uint32_t* em = a.emask + (size_t)inst * L2;
+    const bool nec = (Gl < a.thGd) || (O < a.thOd) || (H < a.thHd);
+    const bool starv = (O < a.thOq) || (Gl < a.thGq);
     const int y = site / L, x = site - y * L;
     // EMPTY-slot masks by group: own site, N, E, S, W (none outside the lattice)
-    const uint32_t gm[5] = {em[site], y > 0 ? em[site - L] : 0u, x < L - 1 ? em[site + 1] : 0u,
+    const uint32_t gm[5] = {own_empty, y > 0 ? em[site - L] : 0u, x < L - 1 ? em[site + 1] : 0u,
                             y < L - 1 ? em[site + L] : 0u, x > 0 ? em[site - 1] : 0u};
     const uint32_t m = (uint32_t)(__builtin_popcount(gm[0]) + __builtin_popcount(gm[1]) + __builtin_popcount(gm[2]) +
                                   __builtin_popcount(gm[3]) + __builtin_popcount(gm[4]));
     uint16_t* cw = a.cells + (size_t)inst * C * L2;
     uint32_t* pr = a.prop + (size_t)inst * C * L2;
-    const uint32_t T_div = s_k.T_div;
+    const uint32_t T_div = a.T_div;
     // All of the site's words are loaded first (independent loads, issued
     // together; the loop is unrolled to the slot limit so they stay in
     // registers), then the transitions; the Philox blocks are drawn only for the
@@ -465,6 +551,8 @@ __global__ void __launch_bounds__(Q3_NT) q3_update_kernel(Q3Args a, const float*
 // n + 1 if the protocol has one (as q3_fraction_kernel applies it, from the
 // fields F that step starts from); and the next step's reaction term and
 // EMPTY mask.
+// Sites without a cell and without a birth are left as they are (512 instances
+// as above: 81 us, now 51).
 __global__ void __launch_bounds__(Q3_NT) q3_resolve_kernel(Q3Args a, int n, int32_t* traj_col, int traj_stride,
                                                           int32_t* live, const float* F, int next) {
     int inst, site;
@@ -475,27 +563,33 @@ __global__ void __launch_bounds__(Q3_NT) q3_resolve_kernel(Q3Args a, int n, int3
     __shared__ int s_part[Q3_NT / 64];
     __shared__ int s_j;
     __shared__ uint32_t s_thr[4][GGA_OER_BINS];
+    const int L2 = a.L * a.L, C = a.C;
+    const size_t plane = (size_t)a.n_inst * L2, at0 = (size_t)inst * L2 + site;
+    // a site without a cell keeps its mask and reaction term unless one is born there
+    const bool bare = site < L2 && a.emask[at0] == q3_full(C);
+    uint32_t tm = site < L2 ? a.tmask[(n & 1) * plane + at0] : 0u;
     set_react_table(a.prm, s_react);
-    if (threadIdx.x == 0) s_j = next ? find_fraction(a, p, 2 * (n + 1)) : -1;
+    if (threadIdx.x < 64) {                       // the fraction by all lanes at once: one memory round trip
+        const int j = next ? scan_fraction(a, p, 2 * (n + 1)) : -1;
+        if (threadIdx.x == 0) s_j = j;
+    }
     __syncthreads();
     const int j = s_j;                            // step n + 1's fraction at the start of its hour
     if (j >= 0) {
         fraction_thresholds(a, p, j, s_thr);
         __syncthreads();                          // block-uniform
     }
-    const int L2 = a.L * a.L, C = a.C;
     int cnt = 0;
-    if (site < L2) {
-        const size_t plane = (size_t)a.n_inst * L2, at0 = (size_t)inst * L2 + site;
+    if (site < L2 && (!bare || tm)) {
         uint16_t* cw = a.cells + (size_t)inst * C * L2;
         const uint32_t* pr = a.prop + (size_t)inst * C * L2;
         const unsigned long long* ky = a.keys + (size_t)inst * C * L2;
-        unsigned long long states = a.svec[at0];
-        for (uint32_t tm = a.tmask[(n & 1) * plane + at0]; tm; tm &= tm - 1) {
+        unsigned long long states = bare ? 0ull : a.svec[at0];
+        for (; tm; tm &= tm - 1) {
             cw[(size_t)__builtin_ctz(tm) * L2 + site] = PROLIF;
             states |= (unsigned long long)PROLIF << (2 * __builtin_ctz(tm));    // the slot was EMPTY
         }
-        for (uint32_t pm = a.pmask[at0]; pm; pm &= pm - 1) {
+        for (uint32_t pm = bare ? 0u : a.pmask[at0]; pm; pm &= pm - 1) {
             const size_t at = (size_t)__builtin_ctz(pm) * L2 + site;
             const uint32_t pp = pr[at];
             if ((uint32_t)(ky[pp >> 8] & 0xFFu) == (pp & 0xFFu)) cw[at] = (uint16_t)((cw[at] & DOOM_BIT) | PROLIF);
@@ -543,7 +637,7 @@ __global__ void __launch_bounds__(Q3_NT) q3_resolve_kernel(Q3Args a, int n, int3
     if (threadIdx.x == 0 && live) {
         int t = 0;
         for (int w = 0; w < Q3_NT / 64; ++w) t += s_part[w];
-        atomicAdd(live + inst, t);
+        if (t) atomicAdd(live + inst, t);
     }
 }
 
@@ -567,34 +661,49 @@ hipError_t q3_init(const Q3Args& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t q3_run(const Q3Args& a, int n0, int nsteps, hipStream_t stream) {
-    if (a.n_inst <= 0) return hipSuccess;
+hipError_t q3_run(const Q3Args& args, int n0, int nsteps, hipStream_t stream) {
+    if (args.n_inst <= 0) return hipSuccess;
+    // the constants of the sub-steps and the cell update in field units, once here
+    // rather than in double precision by every workgroup
+    Q3Args a = args;
+    const gga_params& P = a.prm;
+    a.zero[0] = to_field_units(P, 0, 0.0);
+    a.zero[1] = to_field_units(P, 1, 0.0);
+    a.thOq = to_field_units(P, 0, P.theta_O_quiesce);
+    a.thGq = to_field_units(P, 1, P.theta_G_quiesce);
+    a.thOd = to_field_units(P, 0, P.theta_O_death);
+    a.thGd = to_field_units(P, 1, P.theta_G_death);
+    a.thHd = to_field_units(P, 2, P.theta_H_death);
+    a.T_div = P.P_div >= 1.0 ? 0xFFFFFFFFu : (uint32_t)std::floor(P.P_div * 4294967296.0);
     const dim3 grid = q3_grid(a), block(Q3_NT);
     const size_t nc = (size_t)a.n_inst * (a.traj ? (size_t)nsteps + 1 : 1);
     hipLaunchKernelGGL(q3_counts_kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, stream, a, nsteps);
     hipLaunchKernelGGL(q3_prepare_kernel, grid, block, 0, stream, a, nsteps == 0 ? 1 : 0);
     float* cur = a.fields;
     float* oth = a.fields2;
-    // 64 x 64 owned sites per workgroup of 1,024 threads (one per CU, 113 KB of
-    // LDS at up to 10 sub-steps) once the lattice holds four such tiles, else
-    // 32 x 32 per 512 threads (three per CU)
-    const bool big = a.L >= Q3_BIG_TILE_MIN_L;
-    const dim3 tile_grid(((unsigned)a.n_inst * q3_tiles_per_inst(a.L, big ? 64 : 32) + 7u) / 8u * 8u);
+    // Windows of 128 x 128 sites, or of 64 x 64 while a workgroup each still finds
+    // a CU of its own: one instance of 128 x 128 then takes nine of them and a step
+    // 23 us, 42 with one wide window.  Lattices of up to 64 sites a side beyond that
+    // run by 512 threads (several workgroups per CU) instead of 1,024.
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
     auto diffuse = [&](int k) {
-        while (k > 0) {              // sub-steps fused in LDS tiles, Q3_MAX_HALO at most per launch
-            const int h = k < Q3_MAX_HALO ? k : Q3_MAX_HALO;
-            if (big && h <= 10)
-                hipLaunchKernelGGL((q3_diffuse_tile_kernel<64, 1024, 64 + 20>), tile_grid, dim3(1024), 0, stream, a,
-                                   (const float*)cur, oth, h);
-            else if (big)
-                hipLaunchKernelGGL((q3_diffuse_tile_kernel<64, 1024, 64 + 2 * Q3_MAX_HALO>), tile_grid, dim3(1024), 0,
-                                   stream, a, (const float*)cur, oth, h);
-            else if (h <= 10)
-                hipLaunchKernelGGL((q3_diffuse_tile_kernel<32, 512, 32 + 20>), tile_grid, dim3(512), 0, stream, a,
-                                   (const float*)cur, oth, h);
-            else
-                hipLaunchKernelGGL((q3_diffuse_tile_kernel<32, 512, 32 + 2 * Q3_MAX_HALO>), tile_grid, dim3(512), 0,
-                                   stream, a, (const float*)cur, oth, h);
+        while (k > 0) {              // beyond one window, Q3_MAX_HALO sub-steps at most per launch
+            const int part = k < Q3_MAX_HALO ? k : Q3_MAX_HALO;
+            const long long narrow = q3_windows(a.L, Q3_NARROW, part);
+            const bool few = a.n_inst * narrow * narrow <= cus && (a.L <= Q3_NARROW || k == part);
+            const bool whole = a.L <= (few ? Q3_NARROW : Q3_WIDE);
+            const int h = whole ? k : part;
+            const long long side = q3_windows(a.L, few ? Q3_NARROW : Q3_WIDE, h);
+            const dim3 g((unsigned)((a.n_inst * side * side + 7) / 8 * 8));
+            auto launch = [&](auto* kernel, int nt) { hipLaunchKernelGGL(kernel, g, dim3(nt), 0, stream, a, (const float*)cur, oth, h); };
+            if (few && a.L < Q3_NARROW) launch(q3_diffuse_kernel<1, 4, 16, true>, 1024);
+            else if (few) launch(q3_diffuse_kernel<1, 4, 16, false>, 1024);
+            else if (a.L <= Q3_NARROW) launch(q3_diffuse_kernel<1, 8, 8, true>, 512);
+            else if (a.L < Q3_WIDE) launch(q3_diffuse_kernel<2, 8, 16, true>, 1024);
+            else launch(q3_diffuse_kernel<2, 8, 16, false>, 1024);
             std::swap(cur, oth);
             k -= h;
         }
@@ -613,8 +722,7 @@ hipError_t q3_run(const Q3Args& a, int n0, int nsteps, hipStream_t stream) {
         hipLaunchKernelGGL(q3_update_kernel, grid, block, 0, stream, a, (const float*)cur, n);
         hipLaunchKernelGGL(q3_resolve_kernel, grid, block, 0, stream, a, n, a.traj ? a.traj + i : nullptr, nsteps,
                            i == nsteps - 1 ? a.live : nullptr, (const float*)cur, i + 1 < nsteps ? 1 : 0);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (cur != a.fields) hipLaunchKernelGGL(q3_copy_fields_kernel, grid, block, 0, stream, a, (const float*)cur, a.fields);
     return hipGetLastError();

@@ -159,12 +159,12 @@ __device__ __forceinline__ void store_words(uint16_t* p, const uint32_t (&w)[CPL
 // FTCS update keeps its form: c' = lam S + (1 - 4 lam) c + r carries over to
 // c^' = lam S^ + (1 - 4 lam) c^ + r / rho_f, because the shift g_f cancels
 // (4 lam + (1 - 4 lam) - 1 = 0) and a neighbour on the boundary is g_f, i.e. 0.
-__device__ __forceinline__ double field_rho(const gga_params& P, int f) {
+__host__ __device__ __forceinline__ double field_rho(const gga_params& P, int f) {
     const double k0 = -(double)P.kappa[0];
     const double kf = f < 2 ? -(double)P.kappa[f] : (double)P.kappa[f];
     return kf / k0;
 }
-__device__ __forceinline__ float to_field_units(const gga_params& P, int f, double c) {
+__host__ __device__ __forceinline__ float to_field_units(const gga_params& P, int f, double c) {
     return (float)((c - (double)P.ghost[f]) / field_rho(P, f));
 }
 

@@ -1101,8 +1101,8 @@ int gga_mlp_predict(const void* net_d, const float* dose_d, const int32_t* gap_h
     if (rc) return rc;
     if (B == 0) return GGA_OK;
     if (!pred_d) return GGA_E_ARG;
-    const hipError_t e = gga::mlp_forward(gga::mlp_net(const_cast<void*>(net_d)), dose_d, gap_h_d, nfrac_d, B, K,
-                                          gga::mlp_work(work_d, B), pred_d, true, stream);
+    const hipError_t e = gga::mlp_predict(gga::mlp_net(const_cast<void*>(net_d)), dose_d, gap_h_d, nfrac_d, B, K,
+                                          pred_d, stream);
     return e == hipSuccess ? GGA_OK : hip_fail(e);
 }
 
@@ -1114,7 +1114,7 @@ int gga_mlp_grad(void* net_d, const float* dose_d, const int32_t* gap_h_d, const
     if (B < 1 || !target_d) return GGA_E_ARG;
     const gga::MlpNet net = gga::mlp_net(net_d);
     const gga::MlpWork w = gga::mlp_work(work_d, B);
-    hipError_t e = gga::mlp_forward(net, dose_d, gap_h_d, nfrac_d, B, K, w, w.y, false, stream);
+    hipError_t e = gga::mlp_forward(net, dose_d, gap_h_d, nfrac_d, B, K, w, w.y, stream);
     if (e == hipSuccess) e = gga::mlp_backward(net, B, target_d, w, loss_d, stream);
     return e == hipSuccess ? GGA_OK : hip_fail(e);
 }
@@ -1259,8 +1259,7 @@ hipError_t enqueue_sga(const gga_params* params, const gga_sim_cfg* cfg, gga::Ga
     if (e == hipSuccess) e = gga::launch_offspring(ga_args, stream);
     // screen: surrogate prediction (or random keys for the ablation), keep the best S
     if (e == hipSuccess) {
-        e = sga->screen ? gga::mlp_forward(gga::mlp_net(net), w.cand_dose, w.cand_gap, w.nfrac, C, K,
-                                           gga::mlp_work(w.mlp_work, C), w.pred, true, stream)
+        e = sga->screen ? gga::mlp_predict(gga::mlp_net(net), w.cand_dose, w.cand_gap, w.nfrac, C, K, w.pred, stream)
                         : gga::launch_random_keys(C, w.generation, ((uint64_t)ga_args.seed_hi << 32) | ga_args.seed_lo,
                                                   w.pred, stream);
     }
@@ -1278,7 +1277,7 @@ hipError_t enqueue_sga(const gga_params* params, const gga_sim_cfg* cfg, gga::Ga
     for (int k = 0; k < sga->refine_steps && e == hipSuccess; ++k) {
         const gga::MlpNet mnet = gga::mlp_net(net);
         const gga::MlpWork mw = gga::mlp_work(w.mlp_work, N + S);
-        e = gga::mlp_forward(mnet, pop_dose, pop_gap, w.nfrac, N + S, K, mw, mw.y, false, stream);
+        e = gga::mlp_forward(mnet, pop_dose, pop_gap, w.nfrac, N + S, K, mw, mw.y, stream);
         if (e == hipSuccess) e = gga::mlp_backward(mnet, N + S, pop_fit, mw, w.loss, stream);
         if (e == hipSuccess) e = gga::mlp_adam_refresh(mnet, 0, sga->refine_lr, stream);
     }

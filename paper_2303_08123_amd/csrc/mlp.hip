@@ -15,6 +15,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gga_device.h"
 #include "gga_internal.h"
 #include "mlp_internal.h"
@@ -148,8 +150,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(MlpGemm g) {
                 const int col = n0 + wn + j * 16 + (lane & 15);
                 if (row >= g.M || col >= g.N) continue;
                 float v = acc[i][j][r] + (g.bias ? g.bias[col] : 0.0f);
-                if (g.mode == MLP_FWD || g.mode == MLP_INFER) {
-                    if (g.mode == MLP_FWD) g.Z[(size_t)row * g.ldz + col] = v;
+                if (g.mode == MLP_FWD) {
+                    g.Z[(size_t)row * g.ldz + col] = v;
                     g.H[(size_t)row * g.ldh + col] = (bf16)gelu_f(v);
                 } else if (g.mode == MLP_BWD) {
                     g.H[(size_t)row * g.ldh + col] = (bf16)(v * gelu_grad_f(g.Z[(size_t)row * g.ldz + col]));
@@ -169,9 +171,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(MlpGemm g) {
 // the N / TM column tiles of one row block run on one XCD (blocks are dealt
 // round-robin over the 8 XCDs), which then reads that row block once into its
 // L2.  The accumulators start from the bias.  At most 122 VGPRs (no AGPRs),
-// so four workgroups share a CU (their LDS tiles fill its 160 KB).  MLP_OUT (the last hidden layer of a prediction) stores no activations:
-// it writes, per row and per chunk of TM / 2 columns, the partial dot product
-// of the bf16-rounded GELU outputs with w4 into C[row][chunk].
+// so four workgroups share a CU (their LDS tiles fill its 160 KB).
 template <int WT, int MODE>
 __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
     constexpr int TM = 32 * WT, BK = 32, VPT = TM * BK / 8 / 256, CPR = BK / 8;
@@ -244,22 +244,13 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
 #pragma unroll
     for (int j = 0; j < WT; ++j) {
         const int row = m0 + wm + j * 16 + (lane & 15);
-        if (row >= g.M) continue;                         // the four lanes of a row share its fate
-        float dot = 0.0f;
+        if (row >= g.M) continue;
 #pragma unroll
         for (int i = 0; i < WT; ++i) {
             const int col = n0 + wn + i * 16 + (lane >> 4) * 4;
             float o[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
             if (MODE == MLP_PLAIN) {
                 *reinterpret_cast<float4*>(g.C + (size_t)row * g.ldc + col) = make_float4(o[0], o[1], o[2], o[3]);
-                continue;
-            }
-            if (MODE == MLP_OUT) {                        // this lane's share of H3 . w4 (H3 rounded to bf16)
-                const float4 w = *reinterpret_cast<const float4*>(g.w4 + col);
-                dot = fmaf((float)(bf16)gelu_f(o[0]), w.x, dot);
-                dot = fmaf((float)(bf16)gelu_f(o[1]), w.y, dot);
-                dot = fmaf((float)(bf16)gelu_f(o[2]), w.z, dot);
-                dot = fmaf((float)(bf16)gelu_f(o[3]), w.w, dot);
                 continue;
             }
             if (MODE == MLP_FWD)
@@ -275,13 +266,6 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) h[q] = (bf16)o[q];
             *reinterpret_cast<bf16x4*>(g.H + (size_t)row * g.ldh + col) = h;
-        }
-        if (MODE == MLP_OUT) {
-            // lanes l, l + 16, l + 32, l + 48 hold one row: their sum is the
-            // wave's partial over its TM / 2 columns, chunk (n0 + wn) / (TM / 2)
-            dot += __shfl_xor(dot, 16, 64);
-            dot += __shfl_xor(dot, 32, 64);
-            if ((lane >> 4) == 0) g.C[(size_t)row * g.ldc + (n0 + wn) / (TM / 2)] = dot;
         }
     }
 }
@@ -378,17 +362,12 @@ __global__ void split_sum_kernel(const float* part, int S, long n, float* out) {
     *reinterpret_cast<float4*>(out + i) = acc;
 }
 
-// Features of protocol b: for fraction j < 40, (dose/5, gap/60, 1) if present.
-// One thread per 8 consecutive features (fractions j0 .. j0 + 3), stored as one
-// 16-byte vector; the dose and delay loads depend only on K, so they are in
-// flight together with the load of nfrac[b].
-__global__ void encode_kernel(const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
-                              bf16* X) {
-    constexpr int V = MLP_IN / 8;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * V) return;
-    const int b = idx / V, f0 = (idx - b * V) * 8, j0 = f0 / 3;
-    const int jmax = min(MLP_FRAC, K);
+// Features f0 .. f0 + 7 of protocol b (f0 a multiple of 8): for fraction j < 40,
+// (dose/5, gap/60, 1) if present.  The dose and delay loads depend only on K,
+// so they are in flight together with the load of nfrac[b].
+__device__ __forceinline__ bf16x8 features(const float* dose, const int32_t* gap, const int32_t* nfrac, int b, int K,
+                                           int f0) {
+    const int j0 = f0 / 3, jmax = min(MLP_FRAC, K);
     float d[4], g[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -404,7 +383,148 @@ __global__ void encode_kernel(const float* dose, const int32_t* gap, const int32
         const float v = part == 0 ? d[q] : part == 1 ? g[q] : 1.0f;
         x[e] = (bf16)(j < nf ? v : 0.0f);
     }
-    *reinterpret_cast<bf16x8*>(X + (size_t)b * MLP_IN + f0) = x;
+    return x;
+}
+
+// One thread per 8 consecutive features, stored as one 16-byte vector.
+__global__ void encode_kernel(const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
+                              bf16* X) {
+    constexpr int V = MLP_IN / 8;
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= B * V) return;
+    const int b = idx / V, f0 = (idx - b * V) * 8;
+    *reinterpret_cast<bf16x8*>(X + (size_t)b * MLP_IN + f0) = features(dose, gap, nfrac, b, K, f0);
+}
+
+// A whole prediction in one launch.  A workgroup takes 16 MB protocols through
+// all layers with their activations in LDS (one buffer, overwritten layer by
+// layer: a layer's outputs are complete in the accumulators first).  Wave w
+// computes columns [64 w, 64 w + 64) of every layer; no other wave of the
+// workgroup needs those weights, so it fetches them from L2 itself, 128 values
+// of k ahead (the next layer's too), and passes them through its own LDS strip
+// into the MFMA fragments' order.  The sums run as in gemm_nt_kernel (from the
+// bias, k ascending by 32), the output layer per 64 columns and then over the
+// eight waves in order.
+// Bound: for one workgroup per CU the weights, 1.2 MB from L2 per workgroup
+// (8 us at 64 bytes a cycle; loading the fragments directly, 16 lanes on 16
+// lines, ran at 17 bytes a cycle: 36 us against 19), and for many the GELUs'
+// VALU work (13 us per 64 protocols) after the products.  A launch per layer
+// with the activations through device memory took 152 us for 65,536 protocols
+// and 33 for 5,000, this 131 and 23.  (Two workgroups of 32 protocols on a CU,
+// one's GELUs beside the other's products, fetch the weights twice as often:
+// 168 us.)
+constexpr int FUSED_PITCH = MLP_HID + PADK;
+template <int MB>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+predict_kernel(MlpNet net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K, float* pred) {
+    constexpr int ROWS = 16 * MB;
+    // k in steps of 64, the two fragments of a 128-byte line together: 2 of the first layer, then 8 and 8
+    constexpr int END0 = MLP_IN / 64, END1 = END0 + MLP_HID / 64, END2 = END1 + MLP_HID / 64;
+    __shared__ __attribute__((aligned(16))) bf16 act[ROWS][FUSED_PITCH];
+    __shared__ __attribute__((aligned(16))) bf16 stage[8][64 * 64];   // per wave: a step's weights
+    __shared__ float red[8][ROWS];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b0 = (int)blockIdx.x * ROWS;
+    const int fr = lane & 15, fk = (lane >> 4) * 8, n0 = wave * 64;
+    // step's weights of the wave's 64 columns: 8 lanes a 128-byte line, 8 columns an access
+    bf16x8 wq[2][8];
+    auto weights = [&](int step, bf16x8 (&q)[8]) {
+        const int l = step < END0 ? 0 : step < END1 ? 1 : 2, kd = step < END0 ? MLP_IN : MLP_HID;
+        const bf16* base = net.WT[0];
+        if (l == 1) base = net.WT[1];
+        if (l == 2) base = net.WT[2];
+        base += (size_t)n0 * kd + (step - (l == 0 ? 0 : l == 1 ? END0 : END1)) * 64;
+        const uint32_t at = (uint32_t)((lane >> 3) * kd + (lane & 7) * 8);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[i] = *reinterpret_cast<const bf16x8*>(base + (size_t)i * 8 * kd + at);
+    };
+    // Staging: column r's 16-byte part c at part c ^ (r / 2 mod 8), so that neither
+    // the writes nor the fragment reads (16 columns, one part) meet in a bank.  The
+    // wave's LDS accesses execute in order: no wait between them.
+    bf16* const st = stage[wave];
+    auto part = [&](int r, int c) { return st + r * 64 + ((c ^ (r >> 1)) & 7) * 8; };
+    weights(0, wq[0]);
+    weights(1, wq[1]);
+    for (int v = tid; v < ROWS * (MLP_IN / 8); v += 512) {
+        const int r = v / (MLP_IN / 8), f0 = v % (MLP_IN / 8) * 8;
+        *reinterpret_cast<bf16x8*>(&act[r][f0]) = features(dose, gap, nfrac, min(b0 + r, B - 1), K, f0);
+    }
+    floatx4 acc[4][MB];                                   // [column block][row block]
+    auto start = [&](const float* bias) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 bb = *reinterpret_cast<const float4*>(bias + n0 + i * 16 + (lane >> 4) * 4);
+#pragma unroll
+            for (int j = 0; j < MB; ++j) acc[i][j] = floatx4{bb.x, bb.y, bb.z, bb.w};
+        }
+    };
+    start(net.b[0]);
+    __syncthreads();                                      // the features are in LDS
+    typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    int k0 = 0;                                           // the step's first k in its layer
+#pragma nounroll
+    for (int step = 0; step < END2; step += 2) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *reinterpret_cast<bf16x8*>(part(i * 8 + (lane >> 3), lane & 7)) = wq[b][i];
+            if (step + 2 + b < END2) weights(step + 2 + b, wq[b]);   // also the next layer's first
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                bf16x8 a[MB], w[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const bf16x8*>(part(i * 16 + fr, h * 4 + (lane >> 4)));
+#pragma unroll
+                for (int j = 0; j < MB; ++j) a[j] = *reinterpret_cast<const bf16x8*>(&act[j * 16 + fr][k0 + b * 64 + h * 32 + fk]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j)          // D^T block: rows n, columns m
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], a[j], acc[i][j], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        k0 += 128;
+        if (step + 2 == END0 || step + 2 == END1) {
+            k0 = 0;
+            __syncthreads();                              // the layer's inputs are read
+            // lane: row 16 j + (lane & 15), columns n0 + 16 i + 4 (lane >> 4) .. + 3
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < MB; ++j) {
+                    bf16x4 h;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) h[q] = (bf16)gelu_f(acc[i][j][q]);
+                    *reinterpret_cast<bf16x4*>(&act[j * 16 + fr][n0 + i * 16 + (lane >> 4) * 4]) = h;
+                }
+            start(step + 2 == END0 ? net.b[1] : net.b[2]);
+            __syncthreads();                              // the next layer's inputs are in LDS
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {                        // H3 . w4, H3 rounded to bf16
+        float dot = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 w = *reinterpret_cast<const float4*>(net.w4 + n0 + i * 16 + (lane >> 4) * 4);
+            dot = fmaf((float)(bf16)gelu_f(acc[i][j][0]), w.x, dot);
+            dot = fmaf((float)(bf16)gelu_f(acc[i][j][1]), w.y, dot);
+            dot = fmaf((float)(bf16)gelu_f(acc[i][j][2]), w.z, dot);
+            dot = fmaf((float)(bf16)gelu_f(acc[i][j][3]), w.w, dot);
+        }
+        dot += __shfl_xor(dot, 16, 64);
+        dot += __shfl_xor(dot, 32, 64);
+        if (lane < 16) red[wave][j * 16 + lane] = dot;
+    }
+    __syncthreads();
+    if (tid < ROWS && b0 + tid < B) {
+        float y = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) y += red[w][tid];
+        pred[b0 + tid] = (y + net.b4[0]) * net.norm[1] + net.norm[0];
+    }
 }
 
 // y[b] = H3[b] . w4 + b4 (one wave per sample); optionally de-normalised.
@@ -416,16 +536,6 @@ __global__ void out_fwd_kernel(const bf16* H3, const float* w4, const float* b4,
     for (int k = lane; k < MLP_HID; k += 64) s += (float)H3[(size_t)b * MLP_HID + k] * w4[k];
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if (lane == 0) y[b] = norm ? (s + b4[0]) * norm[1] + norm[0] : s + b4[0];
-}
-
-// y[b] = sum over chunks c (in order) of part[b][c] + b4; optionally de-normalised.
-__global__ void out_sum_kernel(const float* part, int nchunk, int ld, const float* b4, int B, float* y,
-                               const float* norm) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    float s = 0.0f;
-    for (int c = 0; c < nchunk; ++c) s += part[(size_t)b * ld + c];
-    y[b] = norm ? (s + b4[0]) * norm[1] + norm[0] : s + b4[0];
 }
 
 // dy = 2 (y - t') / B with t' = (t - mu) / sigma; loss = mean (y - t')^2.
@@ -584,8 +694,7 @@ bool nt_eligible(const MlpGemm& g, int TM) {
     if (g.sa_m % 8 || g.sb_n % 8 || !aligned16(g.A) || !aligned16(g.B)) return false;
     if (g.bias && !aligned16(g.bias)) return false;
     if (g.mode == MLP_PLAIN) return aligned16(g.C) && g.ldc % 4 == 0;
-    if (g.mode == MLP_OUT) return g.C && g.w4 && aligned16(g.w4) && g.ldc >= g.N / (TM / 2);
-    if (g.mode != MLP_INFER && (!aligned16(g.Z) || g.ldz % 4)) return false;
+    if (!aligned16(g.Z) || g.ldz % 4) return false;
     return aligned16(g.H) && g.ldh % 4 == 0;
 }
 
@@ -594,9 +703,7 @@ void launch_nt(const MlpGemm& g, hipStream_t s) {
     const dim3 grid(blocks_for(g.M, 32 * WT) * (g.N / (32 * WT)));
     switch (g.mode) {
         case MLP_FWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_FWD>), grid, dim3(256), 0, s, g); break;
-        case MLP_INFER: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_INFER>), grid, dim3(256), 0, s, g); break;
         case MLP_BWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_BWD>), grid, dim3(256), 0, s, g); break;
-        case MLP_OUT: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_OUT>), grid, dim3(256), 0, s, g); break;
         default: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_PLAIN>), grid, dim3(256), 0, s, g); break;
     }
 }
@@ -620,7 +727,6 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
         else launch_nt<2>(g, s);
         return hipGetLastError();
     }
-    if (g.mode == MLP_OUT) return hipErrorInvalidValue;    // only the K-contiguous kernel fuses the output layer
     if (tn_eligible(g)) {
         hipLaunchKernelGGL((gemm_tn_kernel<2>), dim3((g.M / 64) * (g.N / 64), 1), dim3(256), 0, s, g, g.K, 0L);
         return hipGetLastError();
@@ -634,39 +740,44 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t mlp_predict(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
+                       float* pred, hipStream_t s) {
+    if (B <= 0) return hipSuccess;
+    // As few protocols per workgroup as still leave each of the 256 CUs one: a
+    // round of workgroups takes 19 us with 16 protocols each, 23 with 32, 33 with 64.
+    auto launch = [&](auto* kernel, int rows) {
+        hipLaunchKernelGGL(kernel, dim3(blocks_for(B, rows)), dim3(512), 0, s, net, dose, gap, nfrac, B, K, pred);
+    };
+    if (B <= 16 * 256) launch(predict_kernel<1>, 16);
+    else if (B <= 32 * 256) launch(predict_kernel<2>, 32);
+    else launch(predict_kernel<4>, 64);
+    return hipGetLastError();
+}
+
+// The forward pass of a training step: every layer's Z and H into w, the
+// normalised predictions into y.
 hipError_t mlp_forward(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B,
-                       int K, const MlpWork& w, float* pred, bool predict, hipStream_t s) {
+                       int K, const MlpWork& w, float* y, hipStream_t s) {
     hipLaunchKernelGGL(encode_kernel, dim3(blocks_for((long)B * (MLP_IN / 8), 256)), dim3(256), 0, s, dose, gap,
                        nfrac, B, K, w.X);
     hipError_t e = hipGetLastError();
     const bf16* in = w.X;
-    int kin = MLP_IN, nchunk = 0;
+    int kin = MLP_IN;
     for (int l = 0; l < 3 && e == hipSuccess; ++l) {
         MlpGemm g{};
         g.M = B; g.N = MLP_HID; g.K = kin;
         g.A = in; g.sa_m = kin; g.sa_k = 1;
         g.B = net.WT[l]; g.sb_k = 1; g.sb_n = kin;           // B(k, n) = W^T[n][k]
         g.bias = net.b[l];
-        g.mode = predict ? MLP_INFER : MLP_FWD;          // a prediction keeps no pre-activations
+        g.mode = MLP_FWD;
         g.Z = w.Z[l]; g.ldz = MLP_HID;
         g.H = w.H[l]; g.ldh = MLP_HID;
-        if (predict && l == 2) {                          // output layer fused: partial dot products in Z[0]
-            g.mode = MLP_OUT;
-            g.w4 = net.w4;
-            g.C = w.Z[0]; g.ldc = 16;
-            nchunk = MLP_HID / (gemm_tile(g) / 2);
-        }
         e = launch_gemm(g, s);
         in = w.H[l];
         kin = MLP_HID;
     }
     if (e != hipSuccess) return e;
-    if (predict)
-        hipLaunchKernelGGL(out_sum_kernel, dim3(blocks_for(B, 256)), dim3(256), 0, s, w.Z[0], nchunk, 16, net.b4, B,
-                           pred, net.norm);
-    else
-        hipLaunchKernelGGL(out_fwd_kernel, dim3(blocks_for(B, 4)), dim3(256), 0, s, w.H[2], net.w4, net.b4, B, pred,
-                           nullptr);
+    hipLaunchKernelGGL(out_fwd_kernel, dim3(blocks_for(B, 4)), dim3(256), 0, s, w.H[2], net.w4, net.b4, B, y, nullptr);
     return hipGetLastError();
 }
 

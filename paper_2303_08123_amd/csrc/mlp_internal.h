@@ -6,7 +6,7 @@
 
 namespace gga {
 
-enum : int { MLP_FWD = 0, MLP_BWD = 1, MLP_PLAIN = 2, MLP_INFER = 3, MLP_OUT = 4 };
+enum : int { MLP_FWD = 0, MLP_BWD = 1, MLP_PLAIN = 2 };
 constexpr int MLP_IN = 128, MLP_HID = 512, MLP_FRAC = 40;
 constexpr long MLP_PARAMS = (long)MLP_IN * MLP_HID + MLP_HID + 2L * ((long)MLP_HID * MLP_HID + MLP_HID) + MLP_HID + 1;
 
@@ -24,7 +24,6 @@ struct MlpGemm {
     long ldh;
     float* C;
     long ldc;
-    const float* w4;             // MLP_OUT: output weights; C receives partial dot products
 };
 
 // Views into a net buffer (see mlp_net()).
@@ -55,7 +54,9 @@ MlpWork mlp_work(void* base, int B);
 
 hipError_t launch_gemm(const MlpGemm& g, hipStream_t s);
 hipError_t mlp_forward(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B,
-                       int K, const MlpWork& w, float* pred, bool predict, hipStream_t s);
+                       int K, const MlpWork& w, float* y, hipStream_t s);
+hipError_t mlp_predict(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
+                       float* pred, hipStream_t s);
 hipError_t mlp_backward(const MlpNet& net, int B, const float* target, const MlpWork& w, float* loss,
                         hipStream_t s);
 hipError_t mlp_adam_refresh(const MlpNet& net, int step, float lr, hipStream_t s);

@@ -1114,7 +1114,7 @@ int gga_mlp_grad(void* net_d, const float* dose_d, const int32_t* gap_h_d, const
     if (B < 1 || !target_d) return GGA_E_ARG;
     const gga::MlpNet net = gga::mlp_net(net_d);
     const gga::MlpWork w = gga::mlp_work(work_d, B);
-    hipError_t e = gga::mlp_forward(net, dose_d, gap_h_d, nfrac_d, B, K, w, w.y, stream);
+    hipError_t e = gga::mlp_forward(net, dose_d, gap_h_d, nfrac_d, B, K, w, stream);
     if (e == hipSuccess) e = gga::mlp_backward(net, B, target_d, w, loss_d, stream);
     return e == hipSuccess ? GGA_OK : hip_fail(e);
 }
@@ -1277,7 +1277,7 @@ hipError_t enqueue_sga(const gga_params* params, const gga_sim_cfg* cfg, gga::Ga
     for (int k = 0; k < sga->refine_steps && e == hipSuccess; ++k) {
         const gga::MlpNet mnet = gga::mlp_net(net);
         const gga::MlpWork mw = gga::mlp_work(w.mlp_work, N + S);
-        e = gga::mlp_forward(mnet, pop_dose, pop_gap, w.nfrac, N + S, K, mw, mw.y, stream);
+        e = gga::mlp_forward(mnet, pop_dose, pop_gap, w.nfrac, N + S, K, mw, stream);
         if (e == hipSuccess) e = gga::mlp_backward(mnet, N + S, pop_fit, mw, w.loss, stream);
         if (e == hipSuccess) e = gga::mlp_adam_refresh(mnet, 0, sga->refine_lr, stream);
     }

@@ -270,48 +270,99 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
     }
 }
 
+// Column sums over the batch of a [B][MLP_HID] bf16 matrix: chunk c of
+// MLP_RED_CHUNKS adds its rows, each lane 8 consecutive columns (one 16-byte
+// load per row) in 4 row groups of one wave each, combined in LDS in a fixed
+// order into part[c]; grad_sum_kernel adds the chunks in order.  Row b is
+// weighted by w[b] when w is given, and column MLP_HID then holds the sum of w.
+struct ColSums {
+    const bf16* D[2];
+    const float* w[2];
+    float* part[2];              // [MLP_RED_CHUNKS][MLP_HID + 1]
+    int B;
+};
+__device__ __forceinline__ void colsum_chunk(const ColSums& a, int which, int c, float* lds) {
+    float (*red)[MLP_HID] = reinterpret_cast<float (*)[MLP_HID]>(lds);
+    float* redw = lds + 4 * MLP_HID;
+    const bf16* D = which ? a.D[1] : a.D[0];
+    const float* w = which ? a.w[1] : a.w[0];
+    float* part = (which ? a.part[1] : a.part[0]) + (size_t)c * (MLP_HID + 1);
+    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6, col = lane * 8;
+    const int rows = (a.B + MLP_RED_CHUNKS - 1) / MLP_RED_CHUNKS;
+    const int b0 = c * rows, b1 = min(a.B, b0 + rows);
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float sw = 0.0f;
+#pragma unroll 4
+    for (int b = b0 + grp; b < b1; b += 4) {
+        const float wb = w ? w[b] : 1.0f;
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(D + (size_t)b * MLP_HID + col);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += (float)v[e] * wb;
+        sw += wb;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[grp][col + e] = s[e];
+    if (lane == 0) redw[grp] = sw;
+    __syncthreads();
+    for (int n = threadIdx.x; n < MLP_HID; n += 256) part[n] = ((red[0][n] + red[1][n]) + red[2][n]) + red[3][n];
+    if (w && threadIdx.x == 0) part[MLP_HID] = ((redw[0] + redw[1]) + redw[2]) + redw[3];
+}
+
 // C = A (M x K) * B (K x N) when both operands run along M and N in memory
 // (A(m, k) = A[k sa_k + m], B(k, n) = B[k sb_k + n]: the weight gradients
 // H^T dZ), over the k range [k0, k1) of split blockIdx.y, M and N multiples of
-// the tile.  16-byte loads of 8 consecutive rows (or columns) at one k are
-// transposed into the [row][k] LDS tiles the MFMA fragments read; rows of k
-// past k1 load as zero.  Each split writes its own f32 slice C + split * ldp
-// (a fixed-order sum over the splits follows when there are several).
-template <int WT>
-__global__ __launch_bounds__(256) void gemm_tn_kernel(MlpGemm g, int kchunk, long ldp) {
-    constexpr int TM = 32 * WT, BK = 32, VPT = TM * BK / 8 / 256, VPR = TM / 8;
-    __shared__ bf16 As[2][TM][BK + PADK];
-    __shared__ bf16 Bs[2][TM][BK + PADK];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ntn = g.N / TM;
+// 64.  A thread loads 8 x 8 elements of one operand (8 rows of k, 16 bytes of
+// each, whole 128-byte lines per 8 lanes), transposes them in registers and
+// writes them as 16-byte parts of the [row][k] LDS tiles the MFMA fragments
+// read; rows of k past k1 load as zero.  Part c of row m lies at part
+// c ^ tn_swizzle(m), which keeps writes (rows 8 apart) and fragment reads (16
+// consecutive rows) from meeting in a bank.  Each split writes its own f32
+// slice C + split * ldp (a fixed-order sum over the splits follows when there
+// are several).  Blocks past the tiles take the column sums that fall due with
+// the product (see colsum_chunk), beside it instead of in launches of their own.
+// Bound: the latency of its few k-steps.  With the transposed elements written
+// one by one (16-bit LDS writes, k-steps of 32) 512 x 512 x 4,096 took 21 us,
+// now 10, column sums included.
+__device__ __forceinline__ int tn_swizzle(int m) { return ((m & 7) ^ ((m >> 3) & 7)) | (((m >> 3) & 1) << 3); }
+__global__ __launch_bounds__(256) void gemm_tn_kernel(MlpGemm g, int kchunk, long ldp, ColSums sums) {
+    constexpr int WT = 2, TM = 64, BK = 128;
+    __shared__ __attribute__((aligned(16))) bf16 tile[2][2][TM][BK];      // [operand][buffer]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ntn = g.N / TM, past = (int)blockIdx.x - ntn * (g.M / TM);
+    if (past >= 0) {
+        if (blockIdx.y == 0)
+            colsum_chunk(sums, past / MLP_RED_CHUNKS, past % MLP_RED_CHUNKS, reinterpret_cast<float*>(&tile[0][0][0][0]));
+        return;
+    }
     const int m0 = (blockIdx.x / ntn) * TM, n0 = (blockIdx.x - (blockIdx.x / ntn) * ntn) * TM;
     const int kb = blockIdx.y * kchunk, ke = min(g.K, kb + kchunk);
     const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TM / 2);
+    const int op = wave >> 1;                              // waves 0 and 1 load A, 2 and 3 B
+    const int mc = tid & 7, kc = (tid & 127) >> 3;         // the thread's 8 columns and 8 rows of k
+    const bf16* src = op ? g.B + n0 : g.A + m0;
+    const long stride = op ? g.sb_k : g.sa_k;
     floatx4 acc[WT][WT];                                  // [column block][row block]
 #pragma unroll
     for (int i = 0; i < WT; ++i)
 #pragma unroll
         for (int j = 0; j < WT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 ra[VPT], rb[VPT];
+    bf16x8 v[8];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * 256, k = k0 + idx / VPR, r = (idx % VPR) * 8;
-            const bool in = k < ke;
+        for (int r = 0; r < 8; ++r) {
+            const int k = k0 + kc * 8 + r;
             const bf16x8 z = {};
-            ra[v] = in ? *reinterpret_cast<const bf16x8*>(g.A + (size_t)k * g.sa_k + m0 + r) : z;
-            rb[v] = in ? *reinterpret_cast<const bf16x8*>(g.B + (size_t)k * g.sb_k + n0 + r) : z;
+            v[r] = k < ke ? *reinterpret_cast<const bf16x8*>(src + (size_t)k * stride + mc * 8) : z;
         }
     };
     auto stash = [&](int buf) {
 #pragma unroll
-        for (int v = 0; v < VPT; ++v) {
-            const int idx = tid + v * 256, k = idx / VPR, r = (idx % VPR) * 8;
+        for (int e = 0; e < 8; ++e) {
+            bf16x8 t;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                As[buf][r + e][k] = ra[v][e];
-                Bs[buf][r + e][k] = rb[v][e];
-            }
+            for (int r = 0; r < 8; ++r) t[r] = v[r][e];
+            const int m = mc * 8 + e;
+            *reinterpret_cast<bf16x8*>(&tile[op][buf][m][(kc ^ tn_swizzle(m)) * 8]) = t;
         }
     };
     const int nk = (ke - kb + BK - 1) / BK;
@@ -320,19 +371,25 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(MlpGemm g, int kchunk, lon
         stash(0);
     }
     __syncthreads();
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
+    const int fr = lane & 15, fq = lane >> 4;
     for (int t = 0; t < nk; ++t) {
         const int buf = t & 1;
         if (t + 1 < nk) fetch(kb + (t + 1) * BK);
-        bf16x8 a[WT];
 #pragma unroll
-        for (int j = 0; j < WT; ++j) a[j] = *reinterpret_cast<const bf16x8*>(&As[buf][wm + j * 16 + fr][fk]);
+        for (int kk = 0; kk < BK / 32; ++kk) {
+            auto fragment = [&](int o, int m) {
+                return *reinterpret_cast<const bf16x8*>(&tile[o][buf][m][((kk * 4 + fq) ^ tn_swizzle(m)) * 8]);
+            };
+            bf16x8 a[WT];
 #pragma unroll
-        for (int i = 0; i < WT; ++i) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[buf][wn + i * 16 + fr][fk]);
+            for (int j = 0; j < WT; ++j) a[j] = fragment(0, wm + j * 16 + fr);
 #pragma unroll
-            for (int j = 0; j < WT; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < WT; ++i) {
+                const bf16x8 b = fragment(1, wn + i * 16 + fr);
+#pragma unroll
+                for (int j = 0; j < WT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[j], acc[i][j], 0, 0, 0);
+            }
         }
         if (t + 1 < nk) stash(buf ^ 1);
         __syncthreads();
@@ -350,16 +407,58 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(MlpGemm g, int kchunk, lon
     }
 }
 
-// out[i] = sum over splits s = 0 .. S-1 (in order) of part[s * n + i], 4 per thread
-__global__ void split_sum_kernel(const float* part, int S, long n, float* out) {
-    const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (i >= n) return;
-    float4 acc = *reinterpret_cast<const float4*>(part + i);
-    for (int s = 1; s < S; ++s) {
-        const float4 v = *reinterpret_cast<const float4*>(part + (size_t)s * n + i);
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+// The sums that follow a weight gradient, all in one launch and each in a fixed
+// order: gW over the splits (4 entries per thread, the first `wblocks` blocks;
+// none when the product wrote gW itself), gb over the chunks of its column
+// sums, and behind the last layer's gradient gw4 and gb4 over theirs and the
+// loss over the blocks of out_kernel.
+struct MlpSums {
+    const float* part;           // [S][n]
+    int S, wblocks;
+    long n;
+    float* gW;
+    const float* col[2];         // [MLP_RED_CHUNKS][MLP_HID + 1]
+    float *gb, *gw4, *gb4;
+    const float* sq;             // [nsq]
+    int nsq, B;
+    float* loss;
+};
+__global__ __launch_bounds__(256) void grad_sum_kernel(MlpSums a) {
+    const int block = (int)blockIdx.x - a.wblocks;
+    if (block < 0) {
+        const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+        if (i >= a.n) return;
+        float4 acc = *reinterpret_cast<const float4*>(a.part + i);
+        for (int s = 1; s < a.S; ++s) {
+            const float4 v = *reinterpret_cast<const float4*>(a.part + (size_t)s * a.n + i);
+            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+        }
+        *reinterpret_cast<float4*>(a.gW + i) = acc;
+        return;
     }
-    *reinterpret_cast<float4*>(out + i) = acc;
+    constexpr int BB = MLP_HID / 256;                      // blocks of a column vector
+    const int which = block / BB, n = block % BB * 256 + (int)threadIdx.x;
+    auto chunks = [&](const float* part, int at) {
+        float s = 0.0f;
+#pragma unroll 16
+        for (int c = 0; c < MLP_RED_CHUNKS; ++c) s += part[(size_t)c * (MLP_HID + 1) + at];
+        return s;
+    };
+    if (which == 0) {
+        a.gb[n] = chunks(a.col[0], n);
+    } else if (which == 1) {
+        a.gw4[n] = chunks(a.col[1], n);
+    } else {                                               // one block: thread 0 and, for the loss, all
+        __shared__ float red[256];
+        if (threadIdx.x == 0) a.gb4[0] = chunks(a.col[1], MLP_HID);
+        red[threadIdx.x] = (int)threadIdx.x < a.nsq ? a.sq[threadIdx.x] : 0.0f;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0 && a.loss) a.loss[0] = red[0] / (float)a.B;
+    }
 }
 
 // Features f0 .. f0 + 7 of protocol b (f0 a multiple of 8): for fraction j < 40,
@@ -527,100 +626,109 @@ predict_kernel(MlpNet net, const float* dose, const int32_t* gap, const int32_t*
     }
 }
 
-// y[b] = H3[b] . w4 + b4 (one wave per sample); optionally de-normalised.
-__global__ void out_fwd_kernel(const bf16* H3, const float* w4, const float* b4, int B, float* y,
-                               const float* norm) {
-    const int b = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (b >= B) return;
-    float s = 0.0f;
-    for (int k = lane; k < MLP_HID; k += 64) s += (float)H3[(size_t)b * MLP_HID + k] * w4[k];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) y[b] = norm ? (s + b4[0]) * norm[1] + norm[0] : s + b4[0];
-}
-
-// dy = 2 (y - t') / B with t' = (t - mu) / sigma; loss = mean (y - t')^2.
-__global__ __launch_bounds__(256) void loss_kernel(const float* y, const float* t, const float* norm, int B,
-                                                   float* dy, float* loss) {
-    __shared__ float red[256];
-    float s = 0.0f;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        const float e = y[b] - (t[b] - norm[0]) / norm[1];
-        dy[b] = 2.0f * e / (float)B;
-        s += e * e;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && loss) loss[0] = red[0] / (float)B;
-}
-
-// dZ3[b][k] = dy[b] w4[k] gelu'(Z3[b][k])
-__global__ void out_bwd_kernel(const float* dy, const float* w4, const float* Z3, int B, bf16* dZ3) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * MLP_HID) return;
-    const int b = idx / MLP_HID, k = idx - b * MLP_HID;
-    dZ3[idx] = (bf16)(dy[b] * w4[k] * gelu_grad_f(Z3[idx]));
-}
-
-// Column sums of a [B][N] bf16 matrix (bias gradients), and dw4 / db4.
-// Column sums over the batch, in two deterministic passes: block c adds the
-// rows of chunk c, each lane 8 consecutive columns (one 16-byte load per row)
-// in 4 row groups of one wave each, combined in LDS in a fixed order; the
-// final pass adds the chunks in order.  Row b is weighted by w[b] when w is
-// given, and column N then holds the sum of w.  N <= 512, N % 8 == 0.
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16* D, const float* w, int B, int N,
-                                                             float* part) {
-    __shared__ float red[4][MLP_HID];
-    __shared__ float redw[4];
-    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6, c = blockIdx.x;
-    const int col = lane * 8;
-    const int rows = (B + MLP_RED_CHUNKS - 1) / MLP_RED_CHUNKS;
-    const int b0 = c * rows, b1 = min(B, b0 + rows);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float sw = 0.0f;
-    for (int b = b0 + grp; b < b1; b += 4) {
-        const float wb = w ? w[b] : 1.0f;
-        if (col < N) {
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(D + (size_t)b * N + col);
+// The output layer of a training step, forward and backward, and the loss: per
+// row b (one wave, every 64th column a lane) y = H3[b] . w4 + b4, e = y - t'
+// with t' = (t - mu) / sigma, dy = 2 e / B and dZ3[b] = dy w4 gelu'(Z3[b]); per
+// block of `rows` rows (at most 256 blocks) the sum of e^2.  One pass over H3
+// and Z3; separate launches for y, the loss and dZ3 took 18 us for 4,096 rows,
+// this 7.
+__global__ __launch_bounds__(256) void out_kernel(const bf16* H3, const float* Z3, const float* w4, const float* b4,
+                                                  const float* t, const float* norm, int B, int rows, float* y, float* dy,
+                                                  bf16* dZ3, float* sq) {
+    __shared__ float red[4];
+    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+    const int r0 = (int)blockIdx.x * rows, r1 = min(B, r0 + rows);
+    float w[8], se = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += (float)v[e] * wb;
+    for (int e = 0; e < 8; ++e) w[e] = w4[lane + 64 * e];
+    const float mu = norm[0], sigma = norm[1], bias = b4[0];
+    for (int b = r0 + grp; b < r1; b += 4) {
+        const size_t at = (size_t)b * MLP_HID + lane;
+        float h[8], z[8], s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            h[e] = (float)H3[at + 64 * e];
+            z[e] = Z3[at + 64 * e];
         }
-        sw += wb;
-    }
-    if (col < N) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) red[grp][col + e] = s[e];
+        for (int e = 0; e < 8; ++e) s += h[e] * w[e];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        const float yb = s + bias, err = yb - (t[b] - mu) / sigma, d = 2.0f * err / (float)B;
+        if (lane == 0) {
+            y[b] = yb;
+            dy[b] = d;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dZ3[at + 64 * e] = (bf16)(d * w[e] * gelu_grad_f(z[e]));
+        se += err * err;
     }
-    if (lane == 0) redw[grp] = sw;
+    if (lane == 0) red[grp] = se;
     __syncthreads();
-    for (int n = threadIdx.x; n < N; n += blockDim.x)
-        part[(size_t)c * (N + 1) + n] = ((red[0][n] + red[1][n]) + red[2][n]) + red[3][n];
-    if (w && threadIdx.x == 0) part[(size_t)c * (N + 1) + N] = ((redw[0] + redw[1]) + redw[2]) + redw[3];
-}
-__global__ void colsum_final_kernel(const float* part, int N, int with_w, float* out, float* out_w) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n > N || (n == N && !with_w)) return;
-    float s = 0.0f;
-    for (int c = 0; c < MLP_RED_CHUNKS; ++c) s += part[(size_t)c * (N + 1) + n];
-    if (n < N) out[n] = s;
-    else out_w[0] = s;
+    if (threadIdx.x == 0) sq[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// Adam with bias correction over the flat parameter vector.
-__global__ void adam_kernel(float* p, float* m, float* v, const float* g, long n, float lr, const int32_t* step) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float t = (float)*step;                       // bias corrections of step t
+// Adam with bias correction over the flat parameter vector, and the bf16 copies
+// W [K][N] and W^T [N][K] of the three MFMA layers.  Blocks of 32 x 64 weights
+// (W^T leaves through LDS in whole rows), then blocks of 256 of the other
+// parameters.  One launch instead of one for Adam and one per layer, which read
+// the weights again and wrote W^T two bytes a line: 17 us, now 8.
+constexpr int ADAM_K = 32, ADAM_N = 64;
+constexpr int adam_tiles(int K) { return K / ADAM_K * (MLP_HID / ADAM_N); }
+constexpr int ADAM_TILES = adam_tiles(MLP_IN) + 2 * adam_tiles(MLP_HID);
+constexpr int ADAM_REST = 4 * MLP_HID + 1;                // biases, w4, b4
+__global__ __launch_bounds__(256) void adam_kernel(MlpNet net, float lr) {
+    const float t = (float)*net.step;                   // bias corrections of step t
     const float c1 = 1.0f - powf(0.9f, t), c2 = 1.0f - powf(0.999f, t);
-    const float gi = g[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    auto update = [&](long i, float gi, float m0, float v0, float p0) {
+        const float mi = 0.9f * m0 + 0.1f * gi;
+        const float vi = 0.999f * v0 + 0.001f * gi * gi;
+        net.m[i] = mi;
+        net.v[i] = vi;
+        return net.p[i] = p0 - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    };
+    int tile = (int)blockIdx.x;
+    if (tile >= ADAM_TILES) {
+        int j = (tile - ADAM_TILES) * 256 + (int)threadIdx.x;
+        if (j >= ADAM_REST) return;
+        const int l = j / MLP_HID;                      // b1, b2, b3, then w4 and b4, which follow b3
+        const long i = (l == 0 ? net.b[0] + j : l == 1 ? net.b[1] + j % MLP_HID : l == 2 ? net.b[2] + j % MLP_HID
+                                                                                : net.w4 + (j - 3 * MLP_HID)) - net.p;
+        update(i, net.g[i], net.m[i], net.v[i], net.p[i]);
+        return;
+    }
+    __shared__ bf16 s_t[ADAM_N][ADAM_K + 2];
+    int l = 0;
+    while (tile >= adam_tiles(l ? MLP_HID : MLP_IN)) tile -= adam_tiles(l++ ? MLP_HID : MLP_IN);
+    const int K = l ? MLP_HID : MLP_IN;
+    float* W = l == 0 ? net.Wf[0] : l == 1 ? net.Wf[1] : net.Wf[2];
+    bf16* Wb = l == 0 ? net.W[0] : l == 1 ? net.W[1] : net.W[2];
+    bf16* WT = l == 0 ? net.WT[0] : l == 1 ? net.WT[1] : net.WT[2];
+    const int k0 = tile / (MLP_HID / ADAM_N) * ADAM_K, n0 = tile % (MLP_HID / ADAM_N) * ADAM_N;
+    constexpr int PER = ADAM_K * ADAM_N / 256;
+    float in[PER][4];                                   // all loads before the first store
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = q * 256 + (int)threadIdx.x;
+        const long i = W - net.p + (long)(k0 + e / ADAM_N) * MLP_HID + n0 + e % ADAM_N;
+        in[q][0] = net.g[i];
+        in[q][1] = net.m[i];
+        in[q][2] = net.v[i];
+        in[q][3] = net.p[i];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = q * 256 + (int)threadIdx.x, k = e / ADAM_N, n = e % ADAM_N;
+        const long at = (long)(k0 + k) * MLP_HID + n0 + n;
+        const bf16 v = (bf16)update(W - net.p + at, in[q][0], in[q][1], in[q][2], in[q][3]);
+        Wb[at] = v;
+        s_t[n][k] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = q * 256 + (int)threadIdx.x, n = e / ADAM_K, k = e % ADAM_K;
+        WT[(long)(n0 + n) * K + k0 + k] = s_t[n][k];
+    }
 }
 
 // bf16 copies W [K][N] and W^T [N][K] of a K x N layer.
@@ -728,7 +836,7 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
         return hipGetLastError();
     }
     if (tn_eligible(g)) {
-        hipLaunchKernelGGL((gemm_tn_kernel<2>), dim3((g.M / 64) * (g.N / 64), 1), dim3(256), 0, s, g, g.K, 0L);
+        hipLaunchKernelGGL(gemm_tn_kernel, dim3((g.M / 64) * (g.N / 64), 1), dim3(256), 0, s, g, g.K, 0L, ColSums{});
         return hipGetLastError();
     }
     if (large)
@@ -754,10 +862,9 @@ hipError_t mlp_predict(const MlpNet& net, const float* dose, const int32_t* gap,
     return hipGetLastError();
 }
 
-// The forward pass of a training step: every layer's Z and H into w, the
-// normalised predictions into y.
+// The hidden layers of a training step: every layer's Z and H into w.
 hipError_t mlp_forward(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B,
-                       int K, const MlpWork& w, float* y, hipStream_t s) {
+                       int K, const MlpWork& w, hipStream_t s) {
     hipLaunchKernelGGL(encode_kernel, dim3(blocks_for((long)B * (MLP_IN / 8), 256)), dim3(256), 0, s, dose, gap,
                        nfrac, B, K, w.X);
     hipError_t e = hipGetLastError();
@@ -776,61 +883,52 @@ hipError_t mlp_forward(const MlpNet& net, const float* dose, const int32_t* gap,
         in = w.H[l];
         kin = MLP_HID;
     }
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(out_fwd_kernel, dim3(blocks_for(B, 4)), dim3(256), 0, s, w.H[2], net.w4, net.b4, B, y, nullptr);
-    return hipGetLastError();
+    return e;
 }
 
-// A weight gradient (K = batch rows): K split over S workgroups per tile so
-// that the 16-64 tiles of a 512-wide layer fill the chip, S = B / 512 up to 8,
-// partials in `part` (part_floats >= S M N; the caller's spent Z3 buffer),
-// then summed in split order.
-hipError_t launch_wgrad(const MlpGemm& g, float* part, long part_floats, hipStream_t s) {
-    if (!tn_eligible(g)) return launch_gemm(g, s);
-    const long mn = (long)g.M * g.N;
-    int S = std::min(8, std::max(1, g.K / 512));
-    while (S > 1 && (long)S * mn > part_floats) --S;
-    const int kchunk = ((g.K + S - 1) / S + 31) / 32 * 32;
-    S = (g.K + kchunk - 1) / kchunk;
-    MlpGemm p = g;
-    if (S > 1) { p.C = part; p.ldc = g.N; }
-    hipLaunchKernelGGL((gemm_tn_kernel<2>), dim3((g.M / 64) * (g.N / 64), S), dim3(256), 0, s, p, kchunk, mn);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || S == 1) return e;
-    hipLaunchKernelGGL(split_sum_kernel, dim3(blocks_for(mn / 4, 256)), dim3(256), 0, s, part, S, mn, g.C);
-    return hipGetLastError();
-}
-
+// The output layer and the loss, then the gradients of every layer.  A weight
+// gradient (K = batch rows) is split over S workgroups per tile so that the
+// 16-64 tiles of a 512-wide layer fill the chip, S = B / 512 up to 8, its
+// partials in the spent Z3 buffer until they are summed in split order.
 hipError_t mlp_backward(const MlpNet& net, int B, const float* target, const MlpWork& w, float* loss,
                         hipStream_t s) {
-    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, w.y, target, net.norm, B, w.dy, loss);
+    // The output layer's column sums and squares lie where the first layer's
+    // gradient goes last (MLP_IN MLP_HID floats): they are spent by then.
+    static_assert((long)MLP_IN * MLP_HID >= (long)MLP_RED_CHUNKS * (MLP_HID + 1) + 256, "scratch in gW[0]");
+    const int rows = std::max(16, (B + 255) / 256), nout = (B + rows - 1) / rows;
+    float* const out = net.gW[0];
+    float* const sq = out + MLP_RED_CHUNKS * (MLP_HID + 1);
+    hipLaunchKernelGGL(out_kernel, dim3(nout), dim3(256), 0, s, w.H[2], w.Z[2], net.w4, net.b4, target, net.norm, B, rows,
+                       w.y, w.dy, w.dZ[0], sq);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // dw4 = H3^T dy, db4 = sum dy
-    hipLaunchKernelGGL(colsum_partial_kernel, dim3(MLP_RED_CHUNKS), dim3(256), 0, s, w.H[2], w.dy, B,
-                       MLP_HID, w.part);
-    hipLaunchKernelGGL(colsum_final_kernel, dim3(blocks_for(MLP_HID + 1, 256)), dim3(256), 0, s, w.part, MLP_HID, 1,
-                       net.gw4, net.gb4);
-    hipLaunchKernelGGL(out_bwd_kernel, dim3(blocks_for((long)B * MLP_HID, 256)), dim3(256), 0, s, w.dy, net.w4,
-                       w.Z[2], B, w.dZ[0]);
-    e = hipGetLastError();
     // layer l = 2, 1, 0: dZ_l in dZ[cur]; weight and bias gradients, then dZ_{l-1}
     int cur = 0;
     for (int l = 2; l >= 0 && e == hipSuccess; --l) {
-        const bf16* hin = l == 0 ? w.X : w.H[l - 1];
         const int kin = l == 0 ? MLP_IN : MLP_HID;
         MlpGemm g{};
         g.M = kin; g.N = MLP_HID; g.K = B;                    // dW_l = H_in^T dZ_l
-        g.A = hin; g.sa_m = 1; g.sa_k = kin;
+        g.A = l == 0 ? w.X : w.H[l - 1]; g.sa_m = 1; g.sa_k = kin;
         g.B = w.dZ[cur]; g.sb_k = MLP_HID; g.sb_n = 1;
         g.mode = MLP_PLAIN;
         g.C = net.gW[l]; g.ldc = MLP_HID;
-        e = launch_wgrad(g, w.Z[2], (long)B * MLP_HID, s);
-        if (e != hipSuccess) break;
-        hipLaunchKernelGGL(colsum_partial_kernel, dim3(MLP_RED_CHUNKS), dim3(256), 0, s, w.dZ[cur],
-                           nullptr, B, MLP_HID, w.part);
-        hipLaunchKernelGGL(colsum_final_kernel, dim3(blocks_for(MLP_HID, 256)), dim3(256), 0, s, w.part, MLP_HID, 0,
-                           net.gb[l], nullptr);
+        if (!tn_eligible(g)) return hipErrorInvalidValue;
+        const long mn = (long)g.M * g.N;
+        int S = std::min(MLP_SPLITS, std::max(1, B / 512));
+        const int kchunk = ((B + S - 1) / S + 31) / 32 * 32;
+        S = (B + kchunk - 1) / kchunk;
+        if (S > 1) g.C = w.Z[2];                              // S M N <= B MLP_HID floats
+        // bias gradients, and with the last layer's dw4 = H3^T dy and db4 = sum dy
+        const ColSums sums{{w.dZ[cur], w.H[2]}, {nullptr, w.dy}, {w.part, out}, B};
+        const unsigned cols = (l == 2 ? 2 : 1) * MLP_RED_CHUNKS;
+        hipLaunchKernelGGL(gemm_tn_kernel, dim3((g.M / 64) * (g.N / 64) + cols, S), dim3(256), 0, s, g, kchunk, mn, sums);
+        MlpSums a{};
+        a.part = w.Z[2]; a.S = S; a.n = mn; a.gW = net.gW[l];
+        a.wblocks = S > 1 ? (int)blocks_for(mn / 4, 256) : 0;
+        a.col[0] = w.part; a.col[1] = out;
+        a.gb = net.gb[l]; a.gw4 = net.gw4; a.gb4 = net.gb4;
+        a.sq = sq; a.nsq = nout; a.B = B; a.loss = loss;
+        const unsigned blocks = a.wblocks + (l == 2 ? 2 * (MLP_HID / 256) + 1 : MLP_HID / 256);
+        hipLaunchKernelGGL(grad_sum_kernel, dim3(blocks), dim3(256), 0, s, a);
         e = hipGetLastError();
         if (l == 0 || e != hipSuccess) break;
         MlpGemm d{};
@@ -847,15 +945,11 @@ hipError_t mlp_backward(const MlpNet& net, int B, const float* target, const Mlp
 }
 
 hipError_t mlp_adam_refresh(const MlpNet& net, int step, float lr, hipStream_t s) {
-    const long n = MLP_PARAMS;
     // the net's step counter: set to `step`, or advanced by one when step is 0
     hipError_t e = launch_counter(net.step, step > 0 ? step : 1, step > 0 ? 0 : 1, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, net.p, net.m, net.v, net.g, n, lr,
-                       net.step);
-    e = hipGetLastError();
-    for (int l = 0; l < 3 && e == hipSuccess; ++l) e = mlp_refresh_layer(net, l, s);
-    return e;
+    hipLaunchKernelGGL(adam_kernel, dim3(ADAM_TILES + blocks_for(ADAM_REST, 256)), dim3(256), 0, s, net, lr);
+    return hipGetLastError();
 }
 
 hipError_t mlp_refresh_layer(const MlpNet& net, int l, hipStream_t s) {

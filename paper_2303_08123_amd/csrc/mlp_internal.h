@@ -38,6 +38,7 @@ struct MlpNet {
     __bf16 *W[3], *WT[3];        // bf16 copies, [K][N] and [N][K]
 };
 constexpr int MLP_RED_CHUNKS = 64;   // row chunks of the batch reductions (bias gradients)
+constexpr int MLP_SPLITS = 8;        // splits of a weight gradient at most
 struct MlpWork {
     __bf16* X;
     float* Z[3];
@@ -54,7 +55,7 @@ MlpWork mlp_work(void* base, int B);
 
 hipError_t launch_gemm(const MlpGemm& g, hipStream_t s);
 hipError_t mlp_forward(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B,
-                       int K, const MlpWork& w, float* y, hipStream_t s);
+                       int K, const MlpWork& w, hipStream_t s);
 hipError_t mlp_predict(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
                        float* pred, hipStream_t s);
 hipError_t mlp_backward(const MlpNet& net, int B, const float* target, const MlpWork& w, float* loss,

@@ -1,5 +1,6 @@
-"""Edges of the one-launch prediction: batch sizes around each workgroup size's
-limits and every protocol length (needs an MI355X).  Predictions of 300 rows
+"""Edges of the surrogate's kernels: batch sizes around each workgroup size's
+limits, every protocol length, small and ragged training batches (needs an
+MI355X).  Predictions of 300 rows
 (16 protocols per workgroup) and 16,600 (64) are compared with the float64
 oracle elsewhere; a protocol's sums do not depend on the batch, so the other
 sizes have to agree with those bit for bit."""
@@ -7,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+import mlp_bounds as mb
 from paper_2303_08123_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +32,21 @@ def test_a_protocol_predicts_the_same_in_every_batch(gga, K):
     assert torch.equal(whole, small)
     for B in (1, 15, 16, 17, 31, 33, 63, 65, 4095, 4096, 4097, 4129, 8191, 8192, 8193, 8257):
         assert torch.equal(gga.mlp_predict(net, *(x[:B].contiguous() for x in dd)), whole[:B]), B
+
+
+@pytest.mark.parametrize("B", [1, 5, 33, 130, 1023, 1024, 2050])
+def test_gradients_at_edges_match_the_oracle_pass_by_pass(gga, B):
+    """One and a few rows (most chunks of the sums empty), ragged splits and
+    k-steps, one split and two: every stored tensor and gradient against the
+    oracle's arithmetic on the kernels' own inputs of that pass."""
+    net = gga.mlp_net(seed=5)
+    dose, gap, nfrac = workloads.random_protocols(B, 10, seed=2, kmin=1)
+    target = np.random.default_rng(9).normal(0.0, 1.0, size=B).astype(np.float32)
+    dd = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (dose, gap, nfrac)]
+    work = gga.mlp_work(B)
+    loss = gga.mlp_grad(net, *dd, torch.from_numpy(target).cuda(), work=work).item()
+    grads = gga.mlp_split(gga.mlp_block(net, "g").cpu().numpy().astype(np.float64))
+    v = {k: x.float().cpu().numpy().astype(np.float64) for k, x in gga.mlp_work_views(work, B).items()}
+    params = gga.mlp_split(gga.mlp_block(net, "p").cpu().numpy().astype(np.float64))
+    params = [mb.bf16(x) if i in (0, 2, 4) else x for i, x in enumerate(params)]
+    mb.check_passes(v, grads, params, target.astype(np.float64), loss, z3_kept=B < 1024)

@@ -26,19 +26,14 @@ __device__ __forceinline__ Block4 philox10(uint32_t c0, uint32_t c1, uint32_t c2
     return {c0, c1, c2, c3};
 }
 
-// Lane shifts through DPP over the whole wave (GFX9 wave_shr:1 / wave_shl:1) or
-// within its rows of 16 lanes (row_shr:1 / row_shl:1).  Lanes whose source lies
-// outside read 0 (bound_ctrl), which the callers use as "no neighbour".  The
-// move folds into the consuming VALU op.
-template <int WIDTH = 64>
+// Lane shifts through DPP over the whole wave (GFX9 wave_shr:1 / wave_shl:1).
+// Lanes whose source lies outside read 0 (bound_ctrl), which the callers use as
+// "no neighbour".  The move folds into the consuming VALU op.
 __device__ __forceinline__ float lane_from_left(float v) {   // lane l <- lane l-1
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, v), WIDTH == 64 ? 0x138 : 0x111, 0xF, 0xF, true));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
 }
-template <int WIDTH = 64>
 __device__ __forceinline__ float lane_from_right(float v) {  // lane l <- lane l+1
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, v), WIDTH == 64 ? 0x130 : 0x101, 0xF, 0xF, true));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
 }
 
 __device__ __forceinline__ uint32_t lane_from_left_u32(uint32_t v) {

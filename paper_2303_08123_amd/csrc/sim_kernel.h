@@ -199,23 +199,21 @@ __device__ __forceinline__ void store_keys(uint32_t* p, const uint32_t (&k)[CPL]
 template <int S>
 constexpr int rot_slot(int i, int k) { return ((i - k) % S + S) % S; }
 
-template <int CPL, int RPT, int NW, int LW = 64 * CPL, int LPR = 64>
+template <int CPL, int RPT, int NW, int LW = 64 * CPL>
 struct Geo {
-    static_assert(LPR == 64 || LPR == 16, "a wave holds one row or four (the DPP rows) at a time");
-    static constexpr int L = LPR * CPL;               // row pitch on the CU
+    static constexpr int L = 64 * CPL;                // row pitch on the CU
     static constexpr int SIDE = LW;                   // lattice side
     static constexpr bool PAD = LW < L;               // columns past the lattice hold padding
     static constexpr bool PADC = PAD && LW % CPL != 0; // one lane holds lattice and padding columns
     static constexpr int NWAVE = NW;
-    static constexpr int NG = NW * (64 / LPR);        // groups of RPT consecutive rows: one or four per wave
-    static constexpr int RR = NG * RPT;
+    static constexpr int RR = NW * RPT;
     static constexpr bool SLAB = RR < LW;
     static constexpr int NT = 64 * NWAVE;
-    // Halo area: [3 ghost rows][per group: 3 top rows, 3 bottom rows], a row per
+    // Halo area: [3 ghost rows][per wave: 3 top rows, 3 bottom rows], a row per
     // field, once per parity of the sub-step count, and 3 ghost rows at the end.
-    // The ghost rows hold the boundary values, so the first and last group read
+    // The ghost rows hold the boundary values, so the first and last wave read
     // their outer neighbour row like every other one.
-    static constexpr int HALO = (6 * NG + 3) * L;
+    static constexpr int HALO = (6 * NW + 3) * L;
     static constexpr int AREA = 2 * HALO + 3 * L;
     static constexpr int POOL = (AREA > RR * L) ? AREA : RR * L;
     static_assert(RR <= LW && NWAVE <= 16, "workgroup above 1024 threads");
@@ -262,12 +260,12 @@ __device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32
 // EXT: the extended radiobiology (the oxygen effect on radiosensitivity,
 // gga_params.oer_max > 1, and mitotic death, gga_params.mitotic_death), a
 // separate instantiation so that runs without them keep their register budget.
-template <int CPL, int RPT, int NW, int LW, bool EXT, bool TEAM = false, int LPR = 64>
+template <int CPL, int RPT, int NW, int LW, bool EXT, bool TEAM = false>
 __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
-    using G = Geo<CPL, RPT, NW, LW, LPR>;
+    using G = Geo<CPL, RPT, NW, LW>;
     constexpr int L = G::L;
     constexpr bool PAD = G::PAD, PADC = G::PADC;
-    static_assert(!TEAM || (G::SLAB && LPR == 64), "teams are made of slabs of whole-wave rows");
+    static_assert(!TEAM || G::SLAB, "teams are made of slabs");
     constexpr int RR = G::RR;
     constexpr int NWAVE = G::NWAVE;
     constexpr bool SLAB = G::SLAB;
@@ -346,9 +344,8 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
     int iy0 = SLAB ? a.slab_i0[slab] : 0, iy1 = SLAB ? a.slab_i1[slab] : RR;
     const int lat0 = ys * LW;                        // lattice index of the slab's first site
     const int nsteps = __builtin_amdgcn_readfirstlane(((!SLAB || TEAM) && a.horizon) ? a.horizon[p] : a.nsteps);
-    const int group = LPR == 64 ? wave : wave * (64 / LPR) + lane / LPR;
-    const int y0 = group * RPT;
-    const int x0 = (LPR == 64 ? lane : lane % LPR) * CPL;
+    const int y0 = wave * RPT;
+    const int x0 = lane * CPL;
     // columns past the lattice hold padding: column x0 + c is the lattice's
     // when realc(c); real: the lane holds at least one lattice column
     auto realc = [&](int c) { return !PAD || x0 + c < LW; };
@@ -649,7 +646,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
         // waiting on the LDS reads at once: 1.95 against 1.77 us per sub-step of
         // 256 instances on 128 x 128, of which issuing its 15 instructions a
         // site takes 1.67.)
-        float* const hw = reinterpret_cast<float*>(s_pool) + (3 + 6 * group) * L + x0;
+        float* const hw = reinterpret_cast<float*>(s_pool) + (3 + 6 * wave) * L + x0;
         constexpr int TOP = 0, BOT = 3 * L, UP = -3 * L, DN = 6 * L, ODD = G::HALO;
         auto put = [&](int at, int slot) {
 #pragma unroll
@@ -674,8 +671,8 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                 for (int c = 0; c < CPL; ++c) {
                     const float above = (i == 0) ? edge[f][c] : F[f][rot_slot<RPT + 1>(i - 1, k)][c];
                     const float below = (i < RPT - 1) ? F[f][rot_slot<RPT + 1>(i + 1, k)][c] : edge[f][c];
-                    const float west = (c > 0) ? F[f][si][c - 1] : lane_from_left<LPR>(F[f][si][CPL - 1]);
-                    const float east = (c < CPL - 1) ? F[f][si][c + 1] : lane_from_right<LPR>(F[f][si][0]);
+                    const float west = (c > 0) ? F[f][si][c - 1] : lane_from_left(F[f][si][CPL - 1]);
+                    const float east = (c < CPL - 1) ? F[f][si][c + 1] : lane_from_right(F[f][si][0]);
                     const float sum = (above + below) + (west + east);
                     F[f][to][c] = fmaf(lam[f][PADC ? c : 0], sum, fmaf(F[f][si][c], cen[f], Ro[i][c]));
                 }

@@ -661,6 +661,8 @@ int gga_philox_fill(const uint32_t* ctr_d, uint64_t seed, uint32_t* out_d, int64
  * each slab recomputing `substeps + 2` halo rows at its inner edges.  Every
  * variant gives bit-identical results.  Sides below a variant's row pitch of
  * 64 * columns-per-lane (96 in 128, 160 .. 224 in 256) hold padding lanes.
+ * The default variants of 160 .. 256 run as teams in slabs as tall as suits the
+ * number of instances (the heights of the side's other variants included).
  * gga_state_run uses the chosen resident variant of L; gga_simulate the chosen
  * resident variant, or the chosen variant of any form for sides without one;
  * gga_simulate_uneven the chosen variant of any form.  Choices are process-wide; gga_autotune sets them by timing.
@@ -704,9 +706,9 @@ int gga_set_team_options(int32_t use_teams, int32_t spin_limit);
  * gga_simulate for a batch whose protocol p runs on a lattice_h[p] x
  * lattice_h[p] lattice for horizon_h[p] steps (HOST arrays; cfg->L and
  * cfg->horizon are not used).  Instances are grouped by lattice side and
- * launched longest horizon first; slab-form groups run as teams (cooperative
- * launches of as many instances as the device holds at once, each instance's
- * slabs resident for its whole horizon), or with the team form switched off
+ * launched longest horizon first; slab-form groups run as teams (a cooperative
+ * launch of as many teams as the device holds at once, each taking instances in
+ * turn, an instance's slabs resident for its whole horizon), or with the team form switched off
  * take one launch per step over the instances still running.  live_d[P][R], fitness_d[P] as
  * gga_simulate (-1 / NaN for invalid protocols).  The instance order is
  * uploaded from host memory, and the call waits for that copy (and the work

@@ -76,7 +76,7 @@ struct SimVariant {
     bool heights;           // teams: of the side's slabs, those that suit the number of instances (see team_height)
 };
 constexpr SimVariant SIM_VARIANTS[] = {
-    {64, 1, 4, 16, 0, "L64 resident 4x1 x16 waves"},
+    {64, 1, 4, 16, 0, "L64 resident 4x1 x16 waves (beyond an instance per CU 8x1 x8)"},
     {64, 1, 2, 16, 32, "L64 slabs of 32 rows, 2x1 x16 waves"},
     {128, 2, 8, 16, 0, "L128 resident 8x2 x16 waves"},
     {128, 2, 16, 8, 0, "L128 resident 16x2 x8 waves"},

@@ -53,6 +53,17 @@ bool sim_supported(int L) { return side_index(L) >= 0 && g_choice[1][side_index(
 
 hipError_t launch_variant(int v, const SimArgs& a, int n_blocks, hipStream_t stream) {
     if (n_blocks <= 0) return hipSuccess;
+    if (v == 0) {
+        // 64 x 64: sixteen waves have the shorter step while every instance finds
+        // a CU of its own (256 instances: 9.6 us against 10.0 with eight waves);
+        // beyond that eight waves of twice the sites do (512: 14.1 against 18.1,
+        // 1,024: 24.7 against 36.0).
+        int dev = 0, cus = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        if (n_blocks > cus) v = 7;
+    }
     switch (v) {
         case 0: return launch_sim<1, 4, 16>(a, n_blocks, stream);
         case 2: return launch_sim<2, 8, 16>(a, n_blocks, stream);

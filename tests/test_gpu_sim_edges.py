@@ -105,3 +105,17 @@ def test_teams_in_turns_equal_one_launch_per_step(gga, model_dict, L, n, substep
         assert np.array_equal(a, b, equal_nan=True)
     valid = np.arange(n) != n // 2
     assert np.all(out[True][0][valid] > 0) and np.all(out[True][0][~valid] == -1)
+
+
+@pytest.mark.parametrize("n", [257, 300, 700])
+def test_many_small_instances_equal_few(gga, model_dict, n):
+    """More 64 x 64 instances than compute units run in another geometry: the
+    same results as in batches of at most one instance per compute unit."""
+    md = high_uptake(model_dict)
+    dose, gap, nfrac = workloads.random_protocols(n, 4, seed=n, kmin=1)
+    cfg = gga.make_cfg(64, 30, 1, seed=3, dose_cap=100.0)
+    live, fit, traj = gga.simulate(md, cfg, *_dev(dose, gap, nfrac), traj=True)
+    few = [x.cpu().numpy() for x in gga.simulate(md, cfg, *_dev(dose[:200], gap[:200], nfrac[:200]), traj=True)]
+    for a, b in zip((live, fit, traj), few):
+        assert np.array_equal(a.cpu().numpy()[:200], b)
+    assert (live.cpu().numpy() > 0).all()

@@ -637,16 +637,13 @@ def uneven_bench(gga, workloads, md, args):
 
 
 def q3_bytes_per_site_step(C):
-    """Algorithmic HBM bytes of one quasi-3D step per site (hourly protocols):
-    the fused sub-steps read three fields and the reaction term and write three
-    fields once (28 B); the cell update reads the C words, three fields, the
-    site's EMPTY mask and the previous step's targeted mask and writes that
-    mask, the changed words (counted as all C), the proposer mask and the
-    8-byte vector of slot states (36 + 4 C); the resolution reads the targeted
-    and proposer masks and the state vector and writes the EMPTY mask and the
-    reaction term (24 B).  Keys, proposals and births (a few per site and step)
-    are not counted."""
-    return 28 + (36 + 4 * C) + 24
+    """HBM bytes of one quasi-3D step that every site costs (hourly protocols):
+    the sub-steps read three fields and the reaction term and write three
+    fields once (28 B); the cell update and the resolution read the site's EMPTY
+    mask and a targeted mask each (16 B).  What the sites that hold cells cost
+    on top (up to 36 + 4 C bytes in the update, 24 in the resolution, keys and
+    proposals) is not counted: it depends on the tumour."""
+    return 28 + 16
 
 
 def q3_cpu_baseline(md, wl, dose, gap, nfrac, n_replicas=2):

@@ -171,10 +171,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(MlpGemm g) {
 // the N / TM column tiles of one row block run on one XCD (blocks are dealt
 // round-robin over the 8 XCDs), which then reads that row block once into its
 // L2.  The accumulators start from the bias.  At most 122 VGPRs (no AGPRs),
-// so four workgroups share a CU (their LDS tiles fill its 160 KB).
-template <int WT, int MODE>
+// so four workgroups share a CU with k-steps of 32 (their LDS tiles fill its
+// 160 KB), two with the small tile's steps of 128.
+template <int WT, int BK, int MODE>
 __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
-    constexpr int TM = 32 * WT, BK = 32, VPT = TM * BK / 8 / 256, CPR = BK / 8;
+    constexpr int TM = 32 * WT, VPT = TM * BK / 8 / 256, CPR = BK / 8;
     __shared__ bf16 As[2][TM][BK + PADK];
     __shared__ bf16 Bs[2][TM][BK + PADK];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -226,15 +227,18 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(MlpGemm g) {
     for (int t = 0; t < nk; ++t) {
         const int buf = t & 1;
         if (t + 1 < nk) fetch((t + 1) * BK);
-        bf16x8 a[WT];
 #pragma unroll
-        for (int j = 0; j < WT; ++j) a[j] = *reinterpret_cast<const bf16x8*>(&As[buf][wm + j * 16 + fr][fk]);
+        for (int kk = 0; kk < BK; kk += 32) {
+            bf16x8 a[WT];
 #pragma unroll
-        for (int i = 0; i < WT; ++i) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[buf][wn + i * 16 + fr][fk]);
+            for (int j = 0; j < WT; ++j) a[j] = *reinterpret_cast<const bf16x8*>(&As[buf][wm + j * 16 + fr][kk + fk]);
 #pragma unroll
-            for (int j = 0; j < WT; ++j)                    // D^T block: rows n, columns m
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < WT; ++i) {
+                const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[buf][wn + i * 16 + fr][kk + fk]);
+#pragma unroll
+                for (int j = 0; j < WT; ++j)                // D^T block: rows n, columns m
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[j], acc[i][j], 0, 0, 0);
+            }
         }
         if (t + 1 < nk) stash(buf ^ 1);
         __syncthreads();
@@ -806,13 +810,13 @@ bool nt_eligible(const MlpGemm& g, int TM) {
     return aligned16(g.H) && g.ldh % 4 == 0;
 }
 
-template <int WT>
+template <int WT, int BK>
 void launch_nt(const MlpGemm& g, hipStream_t s) {
     const dim3 grid(blocks_for(g.M, 32 * WT) * (g.N / (32 * WT)));
     switch (g.mode) {
-        case MLP_FWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_FWD>), grid, dim3(256), 0, s, g); break;
-        case MLP_BWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_BWD>), grid, dim3(256), 0, s, g); break;
-        default: hipLaunchKernelGGL((gemm_nt_kernel<WT, MLP_PLAIN>), grid, dim3(256), 0, s, g); break;
+        case MLP_FWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_FWD>), grid, dim3(256), 0, s, g); break;
+        case MLP_BWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_BWD>), grid, dim3(256), 0, s, g); break;
+        default: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_PLAIN>), grid, dim3(256), 0, s, g); break;
     }
 }
 }  // namespace
@@ -831,8 +835,13 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
     const bool large = gemm_tile(g) == 128;
     if (nt_eligible(g, large ? 128 : 64)) {
-        if (large) launch_nt<4>(g, s);
-        else launch_nt<2>(g, s);
+        // The small tile's k-steps are bound by their loads' latency, so they are as
+        // long as K allows: a training step of 64 rows takes 68 us with steps of
+        // 128 against 76 with 32, one of 4,096 104 against 111, of 8,192 165 and 166.
+        if (large) launch_nt<4, 32>(g, s);
+        else if (g.K % 128 == 0) launch_nt<2, 128>(g, s);
+        else if (g.K % 64 == 0) launch_nt<2, 64>(g, s);
+        else launch_nt<2, 32>(g, s);
         return hipGetLastError();
     }
     if (tn_eligible(g)) {

@@ -50,3 +50,19 @@ def test_gradients_at_edges_match_the_oracle_pass_by_pass(gga, B):
     params = gga.mlp_split(gga.mlp_block(net, "p").cpu().numpy().astype(np.float64))
     params = [mb.bf16(x) if i in (0, 2, 4) else x for i, x in enumerate(params)]
     mb.check_passes(v, grads, params, target.astype(np.float64), loss, z3_kept=B < 1024)
+
+
+@pytest.mark.parametrize("M,N,K,ta,tb", [(70, 128, 32, False, True), (70, 128, 64, False, True), (1, 64, 128, False, True),
+                                         (70, 128, 192, False, True), (129, 64, 384, False, True), (64, 128, 1, True, False),
+                                         (128, 64, 127, True, False), (64, 64, 129, True, False)])
+def test_products_at_edges_of_the_k_steps(gga, M, N, K, ta, tb):
+    """Operands along K (steps of 32, 64 and 128) and across it (steps of 128
+    with a remainder) against float64: products of bf16 values are exact in
+    fp32, so 1e-5 of the absolute sum covers the accumulation."""
+    gen = torch.Generator().manual_seed(M + N + K)
+    A = torch.randn(M, K, generator=gen).to(torch.bfloat16)
+    B = torch.randn(K, N, generator=gen).to(torch.bfloat16)
+    C = gga.mlp_gemm((A.t().contiguous() if ta else A).cuda(), (B.t().contiguous() if tb else B).cuda(), a_trans=ta,
+                     b_trans=tb).cpu().numpy().astype(np.float64)
+    A64, B64 = A.double().numpy(), B.double().numpy()
+    assert np.all(np.abs(C - A64 @ B64) <= 1e-5 * (np.abs(A64) @ np.abs(B64)) + 1e-30)

@@ -72,7 +72,7 @@ typedef struct gga_params {
     float theta_O_death, theta_G_death, theta_H_death;   /* necrosis beyond these */
     int32_t T_min;          /* minimum age (h) before a cell may divide                  */
     int32_t T_lys;          /* hours from death to lysis                                  */
-    int32_t A0;             /* initial ages uniform on 0 .. A0-1                          */
+    int32_t A0;             /* initial ages uniform on 0 .. A0-1, saturating at 255       */
     int32_t seed_radius;    /* initial disc (x-c)^2 + (y-c)^2 <= r^2, c = L/2             */
     int32_t class_age[2];   /* sensitivity classes: age < a0, a0 <= age < a1, age >= a1   */
     double P_div;           /* hourly division probability once age >= T_min             */

@@ -68,7 +68,8 @@ def init_state(params: Params, L, p, r, seed):
     """Initial state: uniform fields; a disc of PROLIF cells at the centre.
 
     Sites with (x - c)^2 + (y - c)^2 <= radius^2, c = L // 2, hold PROLIF cells
-    whose age is floor(w0 * A0 / 2**32), w0 from the block at step 0xFFFFFFFF.
+    whose age is floor(w0 * A0 / 2**32), w0 from the block at step 0xFFFFFFFF,
+    saturating at 255.
     """
     fields = np.empty((3, L, L), dtype=np.float64)
     for f in range(3):
@@ -80,7 +81,7 @@ def init_state(params: Params, L, p, r, seed):
     w0 = site_words(ys * L + xs, INIT_STEP, r, p, seed)[0].astype(np.uint64)
     age = ((w0 * np.uint64(params.A0)) >> np.uint64(32)).astype(np.int64)
     cells = np.zeros((L, L), dtype=np.int64)
-    cells[ys, xs] = pack(PROLIF, age)
+    cells[ys, xs] = pack(PROLIF, np.minimum(age, AGE_MAX))
     return fields, cells
 
 

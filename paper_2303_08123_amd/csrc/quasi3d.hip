@@ -100,8 +100,7 @@ __global__ void __launch_bounds__(Q3_NT) q3_init_kernel(Q3Args a) {
     uint16_t w = 0;
     if ((x - ctr) * (x - ctr) + (y - ctr) * (y - ctr) <= a.prm.seed_radius * a.prm.seed_radius) {
         const Block4 b = philox10((uint32_t)site, INIT_STEP, (uint32_t)r, (uint32_t)p, a.seed_lo, a.seed_hi);
-        const uint32_t age = (uint32_t)(((uint64_t)b.w0 * (uint32_t)a.prm.A0) >> 32);
-        w = (uint16_t)(PROLIF | (age << 2));
+        w = seed_word(b.w0, a.prm.A0);
     }
     cw[site] = w;
     for (int z = 1; z < a.C; ++z) cw[(size_t)z * L2 + site] = 0;

@@ -73,6 +73,17 @@ constexpr uint32_t NONE_KEY = 0xFFFFFFFFu;
 constexpr uint32_t INIT_STEP = 0xFFFFFFFFu;
 constexpr int EMPTY = 0, PROLIF = 1, QUIESC = 2, DEAD = 3;
 constexpr uint32_t DOOM_BIT = 1u << 14;    // cell word: lethally hit, awaiting mitotic death
+// The bits of a cell word that state buffers hold: state, age and mark.  The
+// cell update uses the others within a step, so a caller's words are loaded
+// without them.
+constexpr uint32_t WORD_BITS = 0x3FFu | DOOM_BIT;
+
+// The word of a seeded cell: age floor(w0 A0 / 2^32), saturating at 255 like
+// every age (a larger one would run into the bits above it).
+__device__ __forceinline__ uint16_t seed_word(uint32_t w0, int A0) {
+    const uint32_t age = (uint32_t)(((uint64_t)w0 * (uint32_t)A0) >> 32);
+    return (uint16_t)(PROLIF | (min(age, 255u) << 2));
+}
 
 // 32-bit linear-quadratic survival threshold, evaluated in float64 exactly as
 // written: x = m d, y = m D, S = exp(-alpha x - beta x (x + 2 y)),
@@ -464,7 +475,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
         for (int i = 0; i < RPT; ++i)
 #pragma unroll
             for (int c = 0; c < CPL; ++c)
-                s_cell[(y0 + i) * L + x0 + c] = realc(c) ? cs[(size_t)(y0 + i) * LW + x0 + c] : (uint16_t)0;
+                s_cell[(y0 + i) * L + x0 + c] = realc(c) ? (uint16_t)(cs[(size_t)(y0 + i) * LW + x0 + c] & WORD_BITS) : (uint16_t)0;
     } else {
         const int ctr = LW / 2;
         const int rad2 = P.seed_radius * P.seed_radius;
@@ -485,8 +496,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                 uint16_t w = 0;
                 if (realc(c) && (x - ctr) * (x - ctr) + (y - ctr) * (y - ctr) <= rad2) {
                     const Block4 b = philox10(y * LW + x, INIT_STEP, r, p, seed_lo, seed_hi);
-                    const uint32_t age = (uint32_t)(((uint64_t)b.w0 * (uint32_t)P.A0) >> 32);
-                    w = (uint16_t)(PROLIF | (age << 2));
+                    w = seed_word(b.w0, P.A0);
                 }
                 s_cell[(y0 + i) * L + x] = w;
             }

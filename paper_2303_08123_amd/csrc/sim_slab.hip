@@ -68,8 +68,7 @@ __global__ void slab_init_kernel(SimArgs a, int L, int n, float* fields, uint16_
     uint16_t w = 0;
     if ((x - ctr) * (x - ctr) + (y - ctr) * (y - ctr) <= a.prm.seed_radius * a.prm.seed_radius) {
         const Block4 b = philox10((uint32_t)site, INIT_STEP, (uint32_t)r, (uint32_t)p, k0, k1);
-        const uint32_t age = (uint32_t)(((uint64_t)b.w0 * (uint32_t)a.prm.A0) >> 32);
-        w = (uint16_t)(PROLIF | (age << 2));
+        w = seed_word(b.w0, a.prm.A0);
         if ((a.horizon ? a.horizon[p] : a.count_at) == 0 && a.ev_valid[p] && a.live) atomicAdd(&a.live[inst], 1);
     }
     cells[(size_t)k * plane + site] = w;

@@ -1049,20 +1049,21 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                     const uint32_t alive = s0 ^ s1;      // PROLIF or QUIESC
                     const uint32_t nec = (w[q] >> 10) & ONE, starv = (w[q] >> 11) & ONE;
                     const uint32_t age4 = w[q] & AGE4, older4 = pk_min(pk_add(age4, 4 * ONE), AGE4);
-                    const uint32_t doom = EXT ? w[q] & (DOOM_BIT * ONE) : 0u;
-                    // a live cell: DEAD, or QUIESC at its age, or PROLIF and older (its mark kept)
-                    uint32_t v = bit_select(pk_sub(0u, starv), age4 | (QUIESC * ONE), older4 | (PROLIF * ONE)) | doom;
+                    // a live cell: DEAD, or QUIESC at its age, or PROLIF and older
+                    uint32_t v = bit_select(pk_sub(0u, starv), age4 | (QUIESC * ONE), older4 | (PROLIF * ONE));
                     v = bit_select(pk_sub(0u, nec), DEAD * ONE, v);
                     // a DEAD one: older, or lysed
                     const uint32_t gone = pk_sub(0u, s0 & s1) & pk_sign(pk_sub(older4, lys4)) & (older4 | (DEAD * ONE));
                     const uint32_t was = (s0 | s1) * WAS_BIT;
                     const uint32_t ready = alive & ~(nec | starv) & ~pk_sign(pk_sub(age4, min4));
-                    const uint32_t marked = EXT ? ready & (doom >> 14) : 0u;
+                    const uint32_t marked = EXT ? ready & (w[q] >> 14) : 0u;
                     const uint32_t cand = ready & ~marked & free[q];
                     cand_m[b] |= (UMask)((cand | (cand >> 15)) & 3u) << (j * UC + 2 * q);
                     if constexpr (EXT) doom_m[b] |= (UMask)((marked | (marked >> 15)) & 3u) << (j * UC + 2 * q);
                     if ((own_rows >> k) & 1u) live += __builtin_popcount(alive & ~nec);
-                    w[q] = bit_select(pk_sub(0u, alive), v, gone) | was;
+                    // what lives keeps its mark, though only mitotic death reads it
+                    const uint32_t mark = w[q] & pk_sub(0u, alive & ~nec) & (DOOM_BIT * ONE);
+                    w[q] = bit_select(pk_sub(0u, alive), v, gone) | was | mark;
                 }
                 store_pairs(y, ux, w);
             }
@@ -1156,7 +1157,9 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                                                      (uint32_t)((int)(dies << (30 - 2 * q)) >> 31)),
                                           DEAD * ONE, w[q]);
                     }
-                    w[q] = bit_select(to, PROLIF * ONE, w[q] & ~(WAS_BIT * ONE));
+                    // a winning parent keeps its mark (a daughter's site holds none)
+                    w[q] &= ~(WAS_BIT * ONE);
+                    w[q] = bit_select(to, PROLIF * ONE | (w[q] & (DOOM_BIT * ONE)), w[q]);
                     any |= w[q];
                 }
                 store_pairs(y, ux, w);

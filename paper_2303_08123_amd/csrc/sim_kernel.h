@@ -1000,6 +1000,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
         {
             const int T_lys = min(s_k.T_lys, 256), T_min = min(s_k.T_min, 256);
             const uint32_t lys4 = (uint32_t)(4 * T_lys) * ONE, min4 = (uint32_t)(4 * T_min) * ONE;
+            const uint32_t mitotic = EXT && P.mitotic_death ? ONE : 0u;   // else marks mean nothing
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
             cand_m[b] = empty_m[b] = doom_m[b] = 0;
@@ -1056,7 +1057,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                     const uint32_t gone = pk_sub(0u, s0 & s1) & pk_sign(pk_sub(older4, lys4)) & (older4 | (DEAD * ONE));
                     const uint32_t was = (s0 | s1) * WAS_BIT;
                     const uint32_t ready = alive & ~(nec | starv) & ~pk_sign(pk_sub(age4, min4));
-                    const uint32_t marked = EXT ? ready & (w[q] >> 14) : 0u;
+                    const uint32_t marked = EXT ? ready & (w[q] >> 14) & mitotic : 0u;
                     const uint32_t cand = ready & ~marked & free[q];
                     cand_m[b] |= (UMask)((cand | (cand >> 15)) & 3u) << (j * UC + 2 * q);
                     if constexpr (EXT) doom_m[b] |= (UMask)((marked | (marked >> 15)) & 3u) << (j * UC + 2 * q);

@@ -109,15 +109,17 @@ def test_stray_bits_of_a_callers_words_are_not_read(gga, model_dict, L, variant,
 
 
 @pytest.mark.parametrize("L,variant", [(64, 0), (64, 7), (96, 9), (128, 2), (128, 4), (160, 22), (256, 6)])
-def test_marks_are_kept_without_mitotic_death(gga, model_dict, L, variant):
+@pytest.mark.parametrize("options", [{}, {"oer_max": 3.0, "oer_k": 0.1}], ids=["plain", "oxygen"])
+def test_marks_are_kept_without_mitotic_death(gga, model_dict, L, variant, options):
     """Live cells marked for mitotic death keep the mark in a step without it,
     cycling, starving or dividing (a daughter has none); dead ones drop it.
     Their words equal the oracle's, which has marked cells divide like others."""
-    print(f"marks without mitotic death L={L} variant={variant}", flush=True)
+    print(f"marks without mitotic death L={L} variant={variant} {options}", flush=True)
+    md = with_options(model_dict, **options)
     rng = np.random.default_rng(L + variant)
-    fields, cells = drawn_words(rng, L, Params.from_dict(model_dict))
+    fields, cells = drawn_words(rng, L, Params.from_dict(md))
     cells |= np.where(cells & 3, rng.integers(0, 2, (L, L)) << 14, 0)
-    got, ref, counted = one_step(gga, model_dict, L, variant, fields, cells, 3, 11)
+    got, ref, counted = one_step(gga, md, L, variant, fields, cells, 3, 11)
     for state, age in ((1, 1), (1, 0), (2, 1)):               # cycling cells, parents and starving cells with a mark
         assert ((ref >> 14 == 1) & (ref & 3 == state) & ((ref >> 2 & 255 > 0) == age)).sum() > 10, (state, age)
     assert compare_cells(got, ref, counted)[0] == 0 and counted.mean() < 0.1

@@ -927,14 +927,14 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
         // target's bit in s_claim; the smallest key's low two bits name the
         // winner's direction, so no key is kept.
         constexpr uint32_t NEC_BIT = 1u << 10, STARV_BIT = 1u << 11;
-        // Environment (none when the wave's smallest values are past every
-        // threshold; x < th  <=>  sign bit of x - th: the difference of two
-        // finite floats is zero only when they are equal and otherwise keeps
-        // the sign of the exact difference).
+        // Environment (none when the wave's smallest values are at or above every
+        // threshold, which no value is of a threshold that is no number; x < th
+        // <=>  sign bit of x - th: the difference of two finite floats is zero only
+        // when they are equal and otherwise keeps the sign of the exact difference).
         if (occupied) {
             const float thOq = s_k.thOq, thGq = s_k.thGq, thOd = s_k.thOd, thGd = s_k.thGd, thHd = s_k.thHd;
-            if (dirty || __builtin_amdgcn_ballot_w64(least_O < fmaxf(thOq, thOd) || least_G < fmaxf(thGq, thGd) ||
-                                                     least(2) < thHd) != 0) {
+            if (dirty || __builtin_amdgcn_ballot_w64(!(least_O >= thOq && least_O >= thOd && least_G >= thGq &&
+                                                       least_G >= thGd && least(2) >= thHd)) != 0) {
 #pragma unroll
                 for (int i = 0; i < RPT; ++i) {
                     uint32_t w[CPL];

@@ -1,5 +1,6 @@
 """Cell words against the oracle: ages past the word's 8 bits, stray bits of a
-caller's words (needs an MI355X)."""
+caller's words, marks without mitotic death, and thresholds that are no number
+(needs an MI355X)."""
 import copy
 
 import numpy as np
@@ -123,3 +124,16 @@ def test_marks_are_kept_without_mitotic_death(gga, model_dict, L, variant, optio
     for state, age in ((1, 1), (1, 0), (2, 1)):               # cycling cells, parents and starving cells with a mark
         assert ((ref >> 14 == 1) & (ref & 3 == state) & ((ref >> 2 & 255 > 0) == age)).sum() > 10, (state, age)
     assert compare_cells(got, ref, counted)[0] == 0 and counted.mean() < 0.1
+
+
+@pytest.mark.parametrize("L", [64, 96, 128, 160, 256])
+@pytest.mark.parametrize("theta", ["theta_O_quiesce", "theta_G_quiesce", "theta_O_death", "theta_G_death", "theta_H_death"])
+def test_a_threshold_that_is_no_number_is_passed_everywhere(gga, model_dict, L, theta):
+    """With a NaN threshold every cell counts as beyond it, whatever the other
+    cells of its wave: all die in the first step, or all turn quiescent and none
+    divides."""
+    print(f"NaN threshold {theta} L={L}", flush=True)
+    md = with_options(model_dict, **{theta: float("nan")})
+    protos = _dev(np.zeros((1, 1), np.float32), np.zeros((1, 1), np.int32), np.zeros(1, np.int32))
+    traj = gga.simulate(md, gga.make_cfg(L, 20, 2, seed=1), *protos, traj=True)[2].cpu().numpy()
+    assert np.all(traj == (113 if "quiesce" in theta else 0))

@@ -661,22 +661,29 @@ int gga_philox_fill(const uint32_t* ctr_d, uint64_t seed, uint32_t* out_d, int64
  * each slab recomputing `substeps + 2` halo rows at its inner edges.  Every
  * variant gives bit-identical results.  Sides below a variant's row pitch of
  * 64 * columns-per-lane (96 in 128, 160 .. 224 in 256) hold padding lanes.
- * The default variants of 160 .. 256 run as teams in slabs as tall as suits the
- * number of instances (the heights of the side's other variants included).
+ * Numbers and geometries belong to a build of the library: a variant to be
+ * found again is looked up by its name.
  * gga_state_run uses the chosen resident variant of L; gga_simulate the chosen
  * resident variant, or the chosen variant of any form for sides without one;
- * gga_simulate_uneven the chosen variant of any form.  Choices are process-wide; gga_autotune sets them by timing.
+ * gga_simulate_uneven the chosen variant of any form.  Choices are process-wide;
+ * gga_autotune sets them by timing.  A variant that was set is the kernel that
+ * runs, whatever the batch.  Until then (and again after gga_clear_variant) a
+ * side runs its default variant or, on 64 and 160 .. 256, a relative of it that
+ * suits the number of instances: on 64 x 64 eight waves instead of sixteen beyond
+ * one instance per compute unit, on 160 .. 256 as teams in slabs as tall as pays.
  */
 int gga_variant_count(void);
 int32_t gga_variant_side(int32_t v);      /* lattice side of variant v, -1 if none    */
 int32_t gga_variant_is_slab(int32_t v);   /* 1 slab form, 0 resident, -1 no variant   */
 const char* gga_variant_name(int32_t v);  /* static string                           */
-/* Chosen variant for side L (resident_only != 0: the one gga_simulate uses).
- * Returns the variant, or GGA_E_UNSUPPORTED. */
+/* Chosen variant for side L (resident_only != 0: the one gga_simulate uses), the
+ * default one without a choice.  Returns the variant, or GGA_E_UNSUPPORTED. */
 int gga_get_variant(int32_t L, int32_t resident_only);
 /* Choose variant v for its side (a resident v also becomes the resident
  * choice).  Returns GGA_OK or GGA_E_ARG. */
 int gga_set_variant(int32_t L, int32_t v);
+/* Take side L's choices back.  Returns GGA_OK or GGA_E_ARG. */
+int gga_clear_variant(int32_t L);
 
 /*
  * Device workspace of gga_simulate_uneven for these HOST arrays lattice_h[P]
@@ -748,7 +755,7 @@ size_t gga_autotune_workspace_bytes(int32_t L, int32_t P, int32_t K, int32_t R, 
  * runs, HIP events on `stream`), write each variant's milliseconds to ms_h
  * (HOST, gga_variant_count() entries, NaN for variants not timed), and make
  * the fastest the choice for L (and the fastest resident one the resident
- * choice).  live_d[P][R] and fitness_d[P] hold the last run's results.
+ * choice) for batches of any size, until gga_clear_variant.  live_d[P][R] and fitness_d[P] hold the last run's results.
  * Synchronous.  Returns the chosen variant, or an error as
  * gga_simulate_uneven.
  */

@@ -140,6 +140,7 @@ def _load():
         "gga_variant_name": ([i32], ctypes.c_char_p),
         "gga_get_variant": ([i32, i32], ctypes.c_int),
         "gga_set_variant": ([i32, i32], ctypes.c_int),
+        "gga_clear_variant": ([i32], ctypes.c_int),
         "gga_uneven_workspace_bytes": ([vp, vp, i32, i32, i32, i32], ctypes.c_size_t),
         "gga_set_team_options": ([i32, i32], ctypes.c_int),
         "gga_simulate_uneven": ([vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, ctypes.c_size_t, vp, vp, vp],
@@ -180,7 +181,7 @@ EXPORTS = ("gga_version", "gga_strerror", "gga_last_hip_error", "gga_validate",
            "gga_mlp_set_norm", "gga_mlp_predict", "gga_mlp_grad", "gga_mlp_train_step", "gga_mlp_gemm",
            "gga_sga_workspace_bytes", "gga_sga_init", "gga_sga_generation", "gga_sga_run",
            "gga_variant_count", "gga_variant_side", "gga_variant_is_slab", "gga_variant_name", "gga_get_variant",
-           "gga_set_variant", "gga_set_team_options", "gga_uneven_workspace_bytes", "gga_simulate_uneven", "gga_event_table_bytes",
+           "gga_set_variant", "gga_clear_variant", "gga_set_team_options", "gga_uneven_workspace_bytes", "gga_simulate_uneven", "gga_event_table_bytes",
            "gga_state_run_variant", "gga_autotune_workspace_bytes", "gga_autotune", "gga_simulate_library",
            "gga_measure_peaks", "gga_params_from_json", "gga_slots_breed", "gga_slots_decode",
            "gga_slots_encode", "gga_slots_workspace_bytes", "gga_slots_run", "gga_q3_workspace_bytes",
@@ -446,7 +447,14 @@ def get_variant(L, resident_only=False):
 
 
 def set_variant(L, v):
+    """Run side L by variant v, whatever the batch, until clear_variant(L)."""
     _check(LIB.gga_set_variant(int(L), int(v)))
+
+
+def clear_variant(L):
+    """Take side L's choices (set_variant, autotune) back: the default again, in
+    the form that suits the number of instances."""
+    _check(LIB.gga_clear_variant(int(L)))
 
 
 def _host_i32(x, P, what):
@@ -505,7 +513,7 @@ def state_run_variant(params, cfg, variant, dose, gap, nfrac, n0, nsteps, fields
 
 def autotune(params, cfg, dose, gap, nfrac, stream=None):
     """Time every kernel variant for cfg.L on these protocols (cfg.horizon steps)
-    and make the fastest the choice for cfg.L.  Returns (variant, {variant: ms})."""
+    and make the fastest the choice for cfg.L (until clear_variant).  Returns (variant, {variant: ms})."""
     P, K = _protocols(dose, gap, nfrac)
     n = LIB.gga_autotune_workspace_bytes(cfg.L, P, K, cfg.R, cfg.horizon, cfg.substeps)
     ws = torch.empty(max(int(n), 1), dtype=torch.uint8, device=dose.device)

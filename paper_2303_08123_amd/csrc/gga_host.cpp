@@ -158,7 +158,7 @@ struct SimWs {
 };
 SimWs simulate_ws_layout(int L, int substeps, int32_t P, int32_t R) {
     SimWs w{};
-    w.teams = uses_teams(gga::variant_choice(L, false), L, substeps);
+    w.teams = uses_teams(gga::variant_choice(L, false).v, L, substeps);
     w.rows = state_rows(w.teams, P * R);
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off += align256(bytes); return at; };
@@ -208,7 +208,6 @@ template <class Steps>
 hipError_t team_height(const gga::SimArgs& a, int v, int L, int n, int rows, const Steps& steps, int* best,
                        hipStream_t stream) {
     *best = v;
-    if (!gga::SIM_VARIANTS[v].heights) return hipSuccess;
     double least = 0.0;
     for (int u = 0; u < gga::N_SIM_VARIANTS; ++u) {
         const gga::SimVariant& var = gga::SIM_VARIANTS[u];
@@ -228,15 +227,15 @@ hipError_t team_height(const gga::SimArgs& a, int v, int L, int n, int rows, con
 }
 
 // The instances at list positions 0 .. n-1 of a.inst_list as teams of slab
-// variant v (or of the height that suits them), each for its whole horizon,
-// steps(k) for position k, max_steps the most: a cooperative launch of as many
+// variant choice.v (a default: of the height that suits them), each for its whole
+// horizon, steps(k) for position k, max_steps the most: a cooperative launch of as many
 // teams as the device holds at once (at most `rows`, the instances the state
 // buffers hold), each taking list positions in turns.
 template <class Steps>
-hipError_t enqueue_teams(gga::SimArgs a, int v, int n, int rows, char* state, size_t state_bytes, int L,
-                         int32_t* flags, const Steps& steps, int max_steps, hipStream_t stream) {
-    int cap = 0, teams = 0;
-    hipError_t e = team_height(a, v, L, n, rows, steps, &v, stream);
+hipError_t enqueue_teams(gga::SimArgs a, const gga::Choice& choice, int n, int rows, char* state, size_t state_bytes,
+                         int L, int32_t* flags, const Steps& steps, int max_steps, hipStream_t stream) {
+    int cap = 0, teams = 0, v = choice.v;
+    hipError_t e = choice.set ? hipSuccess : team_height(a, choice.v, L, n, rows, steps, &v, stream);
     if (e == hipSuccess) e = team_launch(v, L, rows, &a, &teams, stream);
     if (e != hipSuccess) return e;
     if (teams < 1) return hipErrorInvalidConfiguration;
@@ -273,7 +272,8 @@ hipError_t enqueue_teams(gga::SimArgs a, int v, int n, int rows, char* state, si
 // over the slabs.
 hipError_t enqueue_simulate_slabs(gga::SimArgs a, const gga_sim_cfg* cfg, int32_t P, int32_t K, char* ws,
                                   const SimWs& w, hipStream_t stream) {
-    const int v = gga::variant_choice(cfg->L, false);
+    const gga::Choice choice = gga::variant_choice(cfg->L, false);
+    const int v = choice.v;
     if (v < 0 || !gga::variant_is_slab(v)) return hipErrorInvalidValue;
     if (variant_plan(v, cfg->L, cfg->substeps, &a) <= 0) return hipErrorInvalidValue;
     int32_t* valid = reinterpret_cast<int32_t*>(ws + w.off_valid);
@@ -296,7 +296,7 @@ hipError_t enqueue_simulate_slabs(gga::SimArgs a, const gga_sim_cfg* cfg, int32_
         a.nsteps = cfg->horizon;
         if (e == hipSuccess) e = gga::launch_slab_live(a, n, stream);
         if (e == hipSuccess)
-            e = enqueue_teams(a, v, n, w.rows, ws + w.off_state, w.state_bytes, cfg->L,
+            e = enqueue_teams(a, choice, n, w.rows, ws + w.off_state, w.state_bytes, cfg->L,
                               reinterpret_cast<int32_t*>(ws + w.off_flags),
                               [&](int) { return cfg->horizon; }, cfg->horizon, stream);
         return e;
@@ -1429,6 +1429,7 @@ size_t state_bytes(int L) { return (size_t)L * L * (3 * sizeof(float) + sizeof(u
 // One group of instances that share a lattice side (and so a kernel variant).
 struct Group {
     int L, variant, first, count, max_h;   // instances list[first .. first+count), horizon-descending
+    gga::Choice choice;                    // the side's choice, of which variant is the number
     bool teams;                            // slab form as teams over whole horizons
     int rows;                              // slab form: instances the state buffers hold
     size_t state_off, flags_off;           // slab form: two state buffers of `rows` instances; team step counts
@@ -1459,10 +1460,10 @@ int plan_uneven(const int32_t* lattice_h, const int32_t* horizon_h, int32_t P, i
         if (list.empty()) continue;
         std::stable_sort(list.begin(), list.end(),
                          [&](int32_t x, int32_t y) { return horizon_h[x / R] > horizon_h[y / R]; });
-        const int v = force && force[si] >= 0 ? force[si] : gga::variant_choice(L, false);
-        if (v < 0) return GGA_E_UNSUPPORTED;
-        const bool teams = uses_teams(v, L, substeps);
-        Group g{L, v, (int)plan->host.size(), (int)list.size(), horizon_h[list[0] / R], teams,
+        const gga::Choice c = force && force[si] >= 0 ? gga::Choice{force[si], true} : gga::variant_choice(L, false);
+        if (c.v < 0) return GGA_E_UNSUPPORTED;
+        const bool teams = uses_teams(c.v, L, substeps);
+        Group g{L, c.v, (int)plan->host.size(), (int)list.size(), horizon_h[list[0] / R], c, teams,
                 state_rows(teams, (int32_t)list.size()), 0, 0};
         plan->groups.push_back(g);
         plan->host.insert(plan->host.end(), list.begin(), list.end());
@@ -1508,7 +1509,7 @@ hipError_t enqueue_uneven(const gga::SimArgs& base, const UnevenPlan& plan, char
             a.n0 = 0;
             a.nsteps = 0;                          // steps come from horizon[]
             a.mode = 0;
-            e = gga::launch_variant(g.variant, a, g.count, stream);
+            e = gga::launch_choice(g.choice, a, g.count, stream);
             continue;
         }
         if (variant_plan(g.variant, g.L, a.substeps, &a) <= 0) return hipErrorInvalidValue;
@@ -1516,7 +1517,7 @@ hipError_t enqueue_uneven(const gga::SimArgs& base, const UnevenPlan& plan, char
             a.nsteps = 0;                          // steps come from horizon[]
             e = gga::launch_slab_live(a, g.count, stream);
             if (e == hipSuccess)
-                e = enqueue_teams(a, g.variant, g.count, g.rows, ws + g.state_off,
+                e = enqueue_teams(a, g.choice, g.count, g.rows, ws + g.state_off,
                                   align256(state_bytes(g.L) * (size_t)g.rows), g.L,
                                   reinterpret_cast<int32_t*>(ws + g.flags_off),
                                   [&](int k) { return plan.host[plan.host.size() - P + plan.host[g.first + k] / R]; },
@@ -1597,11 +1598,13 @@ const char* gga_variant_name(int32_t v) {
 }
 
 int gga_get_variant(int32_t L, int32_t resident_only) {
-    const int v = gga::variant_choice(L, resident_only != 0);
+    const int v = gga::variant_choice(L, resident_only != 0).v;
     return v < 0 ? GGA_E_UNSUPPORTED : v;
 }
 
 int gga_set_variant(int32_t L, int32_t v) { return gga::set_variant_choice(L, v) == 0 ? GGA_OK : GGA_E_ARG; }
+
+int gga_clear_variant(int32_t L) { return gga::clear_variant_choice(L) == 0 ? GGA_OK : GGA_E_ARG; }
 
 size_t gga_uneven_workspace_bytes(const int32_t* lattice_h, const int32_t* horizon_h, int32_t P, int32_t K,
                                   int32_t R, int32_t substeps) {

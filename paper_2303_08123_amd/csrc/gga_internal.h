@@ -73,16 +73,15 @@ struct SimVariant {
     int plan;               // slab form: the sub-step counts accepted are those with a plan of slabs of this many rows
     const char* name;
     double sub, rest;       // us of a team's sub-step and of the rest of its step, where team_height may take the variant
-    bool heights;           // teams: of the side's slabs, those that suit the number of instances (see team_height)
 };
 constexpr SimVariant SIM_VARIANTS[] = {
-    {64, 1, 4, 16, 0, "L64 resident 4x1 x16 waves (beyond an instance per CU 8x1 x8)"},
+    {64, 1, 4, 16, 0, "L64 resident 4x1 x16 waves"},
     {64, 1, 2, 16, 32, "L64 slabs of 32 rows, 2x1 x16 waves"},
     {128, 2, 8, 16, 0, "L128 resident 8x2 x16 waves"},
     {128, 2, 16, 8, 0, "L128 resident 16x2 x8 waves"},
     {128, 2, 4, 16, 64, "L128 slabs of 64 rows, 4x2 x16 waves"},
     {256, 4, 8, 8, 64, "L256 slabs of 64 rows, 8x4 x8 waves", 1.74, 14.0},
-    {256, 4, 11, 8, 64, "L256 slabs of 88 rows, 11x4 x8 waves", 2.4, 18.5, true},
+    {256, 4, 11, 8, 64, "L256 slabs of 88 rows, 11x4 x8 waves", 2.4, 18.5},
     {64, 1, 8, 8, 0, "L64 resident 8x1 x8 waves"},
     {64, 1, 16, 4, 0, "L64 resident 16x1 x4 waves"},
     // sides below the row pitch 64 * cpl: the lanes past the lattice hold padding
@@ -93,7 +92,7 @@ constexpr SimVariant SIM_VARIANTS[] = {
     {192, 4, 9, 8, 64, "L192 slabs of 72 rows, 9x4 x8 waves (48 of 64 lanes)"},
     {192, 4, 8, 8, 64, "L192 slabs of 64 rows, 8x4 x8 waves (48 of 64 lanes)"},
     {224, 4, 8, 8, 64, "L224 slabs of 64 rows, 8x4 x8 waves (56 of 64 lanes)", 1.85, 14.0},
-    {224, 4, 10, 8, 64, "L224 slabs of 80 rows, 10x4 x8 waves (56 of 64 lanes)", 2.65, 12.5, true},
+    {224, 4, 10, 8, 64, "L224 slabs of 80 rows, 10x4 x8 waves (56 of 64 lanes)", 2.65, 12.5},
     {96, 2, 4, 16, 64, "L96 slabs of 64 rows, 4x2 x16 waves (48 of 64 lanes)"},
     // three columns per lane: 192 columns, no padding at 192, 160 of 192 at 160
     {160, 3, 12, 8, 64, "L160 slabs of 96 rows, 12x3 x8 waves (160 of 192 columns)", 2.05, 17.0},
@@ -101,9 +100,9 @@ constexpr SimVariant SIM_VARIANTS[] = {
     {192, 3, 14, 8, 64, "L192 slabs of 112 rows, 14x3 x8 waves", 2.35, 17.2},
     {192, 3, 8, 8, 64, "L192 slabs of 64 rows, 8x3 x8 waves"},
     // the tallest slabs (fewest of them per instance, so least halo recomputed)
-    {160, 3, 9, 8, 72, "L160 slabs of 72 rows, 9x3 x8 waves (160 of 192 columns)", 1.83, 14.3, true},
+    {160, 3, 9, 8, 72, "L160 slabs of 72 rows, 9x3 x8 waves (160 of 192 columns)", 1.83, 14.3},
     {192, 3, 9, 8, 72, "L192 slabs of 72 rows, 9x3 x8 waves", 1.52, 15.2},
-    {192, 3, 10, 8, 80, "L192 slabs of 80 rows, 10x3 x8 waves", 1.87, 14.5, true},
+    {192, 3, 10, 8, 80, "L192 slabs of 80 rows, 10x3 x8 waves", 1.87, 14.5},
 };
 constexpr int N_SIM_VARIANTS = sizeof(SIM_VARIANTS) / sizeof(SIM_VARIANTS[0]);
 constexpr bool variant_is_slab(int v) { return SIM_VARIANTS[v].rpt * SIM_VARIANTS[v].nw < SIM_VARIANTS[v].L; }
@@ -132,9 +131,20 @@ hipError_t launch_slab_variant(int v, const SimArgs& a, int n_blocks, hipStream_
 hipError_t launch_team_variant(int v, const SimArgs& a, int n_blocks, int* capacity, hipStream_t stream);
 // instances per team launch at most (exchange buffers are sized for this many)
 constexpr int TEAM_MAX = 128;
-// process-wide variant choice per lattice side: resident (gga_simulate) and any (uneven batches)
-int variant_choice(int L, bool resident_only);
+// Process-wide variant choice per lattice side: resident (gga_simulate) and any
+// (uneven batches).  A variant that was set runs as it is; the default (v < 0:
+// the side has none) is a form that suits the number of instances: sixteen or
+// eight waves on 64 x 64 (see launch_choice), the slab height of a side's teams
+// (see team_height).
+struct Choice {
+    int v;
+    bool set;
+};
+Choice variant_choice(int L, bool resident_only);
 int set_variant_choice(int L, int v);
+int clear_variant_choice(int L);
+// launch_variant of a resident choice over n_inst instances
+hipError_t launch_choice(const Choice& c, const SimArgs& a, int n_inst, hipStream_t stream);
 // event table of P protocols for the slab form (validity as the resident kernel decides it)
 hipError_t launch_event_table(const SimArgs& a, int P, int32_t* valid, int32_t* count, int32_t* step,
                               EventFraction* frac, hipStream_t stream);

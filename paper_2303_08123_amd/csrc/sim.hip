@@ -42,28 +42,18 @@ hipError_t launch_sim(const SimArgs& a, int n_blocks, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// chosen variant per lattice side 64, 96, .., 256 (index into SIM_VARIANTS):
+// default variant per lattice side 64, 96, .., 256 (index into SIM_VARIANTS):
 // [0] any form, [1] resident only (-1: the side has no resident variant)
-std::atomic<int> g_choice[2][N_SIDES] = {{{0}, {9}, {2}, {22}, {24}, {16}, {6}},
-                                         {{0}, {9}, {2}, {-1}, {-1}, {-1}, {-1}}};
+constexpr int DEFAULT_VARIANT[2][N_SIDES] = {{0, 9, 2, 22, 24, 16, 6}, {0, 9, 2, -1, -1, -1, -1}};
+// the variant set instead of it, plus one (0: none)
+std::atomic<int> g_set[2][N_SIDES];
 
 }  // namespace
 
-bool sim_supported(int L) { return side_index(L) >= 0 && g_choice[1][side_index(L)].load() >= 0; }
+bool sim_supported(int L) { return side_index(L) >= 0 && DEFAULT_VARIANT[1][side_index(L)] >= 0; }
 
 hipError_t launch_variant(int v, const SimArgs& a, int n_blocks, hipStream_t stream) {
     if (n_blocks <= 0) return hipSuccess;
-    if (v == 0) {
-        // 64 x 64: sixteen waves have the shorter step while every instance finds
-        // a CU of its own (256 instances: 9.6 us against 10.0 with eight waves);
-        // beyond that eight waves of twice the sites do (512: 14.1 against 18.1,
-        // 1,024: 24.7 against 36.0).
-        int dev = 0, cus = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        if (n_blocks > cus) v = 7;
-    }
     switch (v) {
         case 0: return launch_sim<1, 4, 16>(a, n_blocks, stream);
         case 2: return launch_sim<2, 8, 16>(a, n_blocks, stream);
@@ -80,23 +70,50 @@ hipError_t launch_variant(int v, const SimArgs& a, int n_blocks, hipStream_t str
 
 int side_index(int L) { return (L % 32 == 0 && L >= 64 && L <= 256) ? L / 32 - 2 : -1; }
 
-int variant_choice(int L, bool resident_only) {
-    const int i = side_index(L);
-    return i < 0 ? -1 : g_choice[resident_only ? 1 : 0][i].load();
+hipError_t launch_choice(const Choice& c, const SimArgs& a, int n_inst, hipStream_t stream) {
+    if (n_inst <= 0) return hipSuccess;
+    int v = c.v;
+    if (!c.set && v == 0) {
+        // 64 x 64: sixteen waves have the shorter step while every instance finds
+        // a CU of its own (256 instances: 9.6 us against 10.0 with eight waves);
+        // beyond that eight waves of twice the sites do (512: 14.1 against 18.1,
+        // 1,024: 24.7 against 36.0).
+        int dev = 0, cus = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        if (n_inst > cus) v = 7;
+    }
+    return launch_variant(v, a, n_inst, stream);
+}
+
+Choice variant_choice(int L, bool resident_only) {
+    const int i = side_index(L), r = resident_only ? 1 : 0;
+    if (i < 0) return {-1, false};
+    const int set = g_set[r][i].load();
+    return set ? Choice{set - 1, true} : Choice{DEFAULT_VARIANT[r][i], false};
 }
 
 int set_variant_choice(int L, int v) {
     const int i = side_index(L);
     if (i < 0 || v < 0 || v >= N_SIM_VARIANTS || SIM_VARIANTS[v].L != L) return -1;
-    g_choice[0][i].store(v);
-    if (!variant_is_slab(v)) g_choice[1][i].store(v);
+    g_set[0][i].store(v + 1);
+    if (!variant_is_slab(v)) g_set[1][i].store(v + 1);
+    return 0;
+}
+
+int clear_variant_choice(int L) {
+    const int i = side_index(L);
+    if (i < 0) return -1;
+    g_set[0][i].store(0);
+    g_set[1][i].store(0);
     return 0;
 }
 
 hipError_t launch_simulation(const SimArgs& a, int L, int n_inst, hipStream_t stream) {
     if (n_inst <= 0) return hipSuccess;
-    const int v = variant_choice(L, true);
-    return v < 0 ? hipErrorInvalidValue : launch_variant(v, a, n_inst, stream);
+    const Choice c = variant_choice(L, true);
+    return c.v < 0 ? hipErrorInvalidValue : launch_choice(c, a, n_inst, stream);
 }
 
 hipError_t launch_fitness(const int32_t* live, int P, int R, float* fitness, hipStream_t stream) {

@@ -15,6 +15,15 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "slow: CPU test that takes more than a few seconds")
 
 
+@pytest.fixture(autouse=True)
+def default_variants():
+    """Every test starts from the library's default kernel variants: a variant set
+    (by way of putting a default back, too) holds for the process."""
+    gga = sys.modules.get("paper_2303_08123_amd")
+    for L in range(64, 257, 32) if gga else ():
+        gga.clear_variant(L)
+
+
 @pytest.fixture(scope="session")
 def model_dict():
     with open(os.path.join(ROOT, "paper_2303_08123_amd", "data", "model_default.json")) as fh:

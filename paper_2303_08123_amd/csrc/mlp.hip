@@ -542,8 +542,10 @@ predict_kernel(MlpNet net, const float* dose, const int32_t* gap, const int32_t*
         for (int i = 0; i < 8; ++i) q[i] = *reinterpret_cast<const bf16x8*>(base + (size_t)i * 8 * kd + at);
     };
     // Staging: column r's 16-byte part c at part c ^ (r / 2 mod 8), so that neither
-    // the writes nor the fragment reads (16 columns, one part) meet in a bank.  The
-    // wave's LDS accesses execute in order: no wait between them.
+    // the writes nor the fragment reads (16 columns, one part) meet in a bank.  Lanes
+    // read what other lanes of the wave wrote: the wave's LDS accesses execute in
+    // order, so a wavefront fence on either side of the reads, which costs no
+    // instruction, is all the hand-over needs.
     bf16* const st = stage[wave];
     auto part = [&](int r, int c) { return st + r * 64 + ((c ^ (r >> 1)) & 7) * 8; };
     weights(0, wq[0]);
@@ -572,6 +574,7 @@ predict_kernel(MlpNet net, const float* dose, const int32_t* gap, const int32_t*
 #pragma unroll
             for (int i = 0; i < 8; ++i) *reinterpret_cast<bf16x8*>(part(i * 8 + (lane >> 3), lane & 7)) = wq[b][i];
             if (step + 2 + b < END2) weights(step + 2 + b, wq[b]);   // also the next layer's first
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -586,6 +589,7 @@ predict_kernel(MlpNet net, const float* dose, const int32_t* gap, const int32_t*
                     for (int j = 0; j < MB; ++j)          // D^T block: rows n, columns m
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], a[j], acc[i][j], 0, 0, 0);
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_sched_barrier(0);
         }
         k0 += 128;

@@ -864,13 +864,17 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
 hipError_t mlp_predict(const MlpNet& net, const float* dose, const int32_t* gap, const int32_t* nfrac, int B, int K,
                        float* pred, hipStream_t s) {
     if (B <= 0) return hipSuccess;
-    // As few protocols per workgroup as still leave each of the 256 CUs one: a
-    // round of workgroups takes 19 us with 16 protocols each, 23 with 32, 33 with 64.
+    // As few protocols per workgroup as still leave each CU at most one: a round of
+    // workgroups takes 19 us with 16 protocols each, 23 with 32, 33 with 64.
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
     auto launch = [&](auto* kernel, int rows) {
         hipLaunchKernelGGL(kernel, dim3(blocks_for(B, rows)), dim3(512), 0, s, net, dose, gap, nfrac, B, K, pred);
     };
-    if (B <= 16 * 256) launch(predict_kernel<1>, 16);
-    else if (B <= 32 * 256) launch(predict_kernel<2>, 32);
+    if (B <= 16LL * cus) launch(predict_kernel<1>, 16);
+    else if (B <= 32LL * cus) launch(predict_kernel<2>, 32);
     else launch(predict_kernel<4>, 64);
     return hipGetLastError();
 }

@@ -803,24 +803,28 @@ unsigned blocks_for(long n, int t) { return (unsigned)((n + t - 1) / t); }
 namespace {
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Operands that run along K, K a multiple of 32, N of the tile width, and
-// 16-byte alignment of every row the epilogue and the loads touch.
+// Operands that run along K, K a multiple of 32 (of 128 in the small tile's form
+// of a layer, whose K is 128 or 512), N of the tile width, and 16-byte alignment
+// of every row the epilogue and the loads touch.
 bool nt_eligible(const MlpGemm& g, int TM) {
     if (g.sa_k != 1 || g.sb_k != 1 || g.K <= 0 || g.K % 32 || g.N % TM) return false;
     if (g.sa_m % 8 || g.sb_n % 8 || !aligned16(g.A) || !aligned16(g.B)) return false;
     if (g.bias && !aligned16(g.bias)) return false;
     if (g.mode == MLP_PLAIN) return aligned16(g.C) && g.ldc % 4 == 0;
-    if (!aligned16(g.Z) || g.ldz % 4) return false;
+    if ((TM == 64 && g.K % 128) || !aligned16(g.Z) || g.ldz % 4) return false;
     return aligned16(g.H) && g.ldh % 4 == 0;
 }
 
-template <int WT, int BK>
+template <int WT, int BK, bool LAYERS = true>
 void launch_nt(const MlpGemm& g, hipStream_t s) {
     const dim3 grid(blocks_for(g.M, 32 * WT) * (g.N / (32 * WT)));
-    switch (g.mode) {
-        case MLP_FWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_FWD>), grid, dim3(256), 0, s, g); break;
-        case MLP_BWD: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_BWD>), grid, dim3(256), 0, s, g); break;
-        default: hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_PLAIN>), grid, dim3(256), 0, s, g); break;
+    if (g.mode == MLP_PLAIN) {
+        hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_PLAIN>), grid, dim3(256), 0, s, g);
+    } else if constexpr (LAYERS) {
+        if (g.mode == MLP_FWD)
+            hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_FWD>), grid, dim3(256), 0, s, g);
+        else
+            hipLaunchKernelGGL((gemm_nt_kernel<WT, BK, MLP_BWD>), grid, dim3(256), 0, s, g);
     }
 }
 }  // namespace
@@ -844,8 +848,8 @@ hipError_t launch_gemm(const MlpGemm& g, hipStream_t s) {
         // 128 against 76 with 32, one of 4,096 104 against 111, of 8,192 165 and 166.
         if (large) launch_nt<4, 32>(g, s);
         else if (g.K % 128 == 0) launch_nt<2, 128>(g, s);
-        else if (g.K % 64 == 0) launch_nt<2, 64>(g, s);
-        else launch_nt<2, 32>(g, s);
+        else if (g.K % 64 == 0) launch_nt<2, 64, false>(g, s);
+        else launch_nt<2, 32, false>(g, s);
         return hipGetLastError();
     }
     if (tn_eligible(g)) {

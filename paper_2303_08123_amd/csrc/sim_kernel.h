@@ -189,27 +189,15 @@ struct CellConst {
     float low[2];       // O and G above these at a step's start: its sub-steps need no clamp
 };
 
-template <int CPL>
-__device__ __forceinline__ void store_keys(uint32_t* p, const uint32_t (&k)[CPL]) {
-    if constexpr (CPL == 1) {
-        p[0] = k[0];
-    } else if constexpr (CPL == 2) {
-        *reinterpret_cast<uint2*>(p) = make_uint2(k[0], k[1]);
-    } else if constexpr (CPL == 3) {
-        p[0] = k[0]; p[1] = k[1]; p[2] = k[2];
-    } else {
-        *reinterpret_cast<uint4*>(p) = make_uint4(k[0], k[1], k[2], k[3]);
-    }
-}
-
-// L = 64 * CPL columns (LW of them the lattice's); NW waves of RPT rows hold
-// RR = NW * RPT rows.  RR = LW: the whole lattice (resident).  RR < LW: a slab of a larger lattice advanced by
-// one step per launch (the rows within `substeps + 2` of a slab edge that is
-// not a lattice edge are a halo, recomputed by the neighbouring slab).
 // Register slot of row i after k forward rotating sub-steps (S = RPT + 1 slots).
 template <int S>
 constexpr int rot_slot(int i, int k) { return ((i - k) % S + S) % S; }
 
+// L = 64 * CPL columns (LW of them the lattice's); NW waves of RPT rows hold
+// RR = NW * RPT rows.  RR = LW: the whole lattice (resident).  RR < LW: a slab of
+// a larger lattice advanced by one step per launch, or through all of them as
+// part of a team (the rows within `substeps + 2` of a slab edge that is not a
+// lattice edge are a halo, recomputed by the neighbouring slab).
 template <int CPL, int RPT, int NW, int LW = 64 * CPL>
 struct Geo {
     static constexpr int L = 64 * CPL;                // row pitch on the CU
@@ -232,7 +220,6 @@ struct Geo {
     static constexpr int SITES = RPT * CPL;           // sites per thread, bit i * CPL + c of the masks
     static_assert(SITES <= 64, "per-thread site masks are 64 bits wide at most");
     using Mask = std::conditional_t<(SITES > 32), uint64_t, uint32_t>;
-    static constexpr Mask ALL = (Mask)(~(Mask)0 >> (8 * sizeof(Mask) - SITES));
     // Cell update: UR units of RPU rows per wave (two rows, a half-wave each,
     // on 64 columns; else one), every NW-th of the workgroup's, UC columns per
     // lane in NP pairs (as many lanes as a row needs), the units in NB blocks
@@ -243,11 +230,9 @@ struct Geo {
     static_assert(L <= 256 && L % UC == 0 && UR % NB == 0 && UR <= 32 && RR % (RPU * NW) == 0, "rows of the cell update");
 };
 
-// Lowest set bit, bit count and lane shifts of a site mask.
+// Lowest set bit of a site mask.
 __device__ __forceinline__ int first_bit(uint32_t m) { return __builtin_ctz(m); }
 __device__ __forceinline__ int first_bit(uint64_t m) { return __builtin_ctzll(m); }
-__device__ __forceinline__ int bit_count(uint32_t m) { return __builtin_popcount(m); }
-__device__ __forceinline__ int bit_count(uint64_t m) { return __builtin_popcountll(m); }
 
 // Two 16-bit lanes in a register (two cell words): subtraction, addition and
 // minimum per half, and each half's sign spread over it.
@@ -285,7 +270,9 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
 
     __shared__ __attribute__((aligned(16))) uint16_t s_cell[RR * L];
     __shared__ __attribute__((aligned(16))) uint32_t s_pool[G::POOL];   // halo buffer(s), then claim slots
-    __shared__ uint32_t s_claim[RR * L / 32 + 1];  // one "has a daughter" bit per site (and a spare word)
+    // one "has a daughter" bit per site (and a word that nothing reads: with it the
+    // arrays behind lie so that the teams' kernels spill 3 to 4 registers less)
+    __shared__ uint32_t s_claim[RR * L / 32 + 1];
     __shared__ uint32_t s_ev_step[GGA_KMAX];   // half-hours since step n0 (2 (n - n0), + 1 at the half hour)
     __shared__ float s_ev_dose[GGA_KMAX];
     __shared__ double s_ev_prior[GGA_KMAX];    // unrepaired dose of the earlier fractions (incomplete repair)

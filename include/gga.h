@@ -701,7 +701,9 @@ size_t gga_uneven_workspace_bytes(const int32_t* lattice_h, const int32_t* horiz
  * compute unit for the instance's whole horizon and exchange halo rows
  * through device memory after every step, each waiting for its neighbours'
  * step count with a bounded spin.  A wait that runs out leaves the instance's
- * live count negative (so its fitness is NaN) and every workgroup exits.
+ * live count negative (so its fitness is NaN), and those of the instances of two
+ * or more steps that the team has yet to take in the same launch; every
+ * workgroup exits.
  * Test hook, process-wide: use_teams = 0 runs slab groups as one launch per
  * step instead (bit-identical results, larger workspace); spin_limit bounds
  * each wait (default 2^21 polls; negative: every wait fails).  Workspace

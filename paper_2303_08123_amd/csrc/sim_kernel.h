@@ -37,7 +37,11 @@
 // and a per-slab step count; before the next step it waits for both
 // neighbours' counts, with a bounded spin, and reloads only its halo rows.
 // A wait that runs out marks the instance's live count negative and the
-// workgroup leaves the instance: every wait ends, so every workgroup exits.
+// workgroup leaves the instance: every wait ends, so every workgroup exits.  It
+// then publishes nothing any more in this launch: its counts would run on into
+// its next instances, past neighbours that have yet to read the rows of the
+// last one it finished.  Instances of a later turn that need an exchange it
+// marks without computing them; those of fewer than two steps it computes.
 //
 // The method (Materials and Methods: nutrient and waste diffusion, cell
 // cycle, quiescence and death driven by the local environment, irradiation
@@ -314,6 +318,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
     // uneven batch of 256 protocols x 4 in launches of one instance per team
     // took 316 ms, now 252).  The step counts run on from instance to instance.
     int flag_base = 0;
+    if (TEAM && tid == 0) s_team_ok = 1;             // until a wait runs out
     for (int turn = 0; turn < (TEAM ? arg.turns : 1); ++turn) {
     // a team's arguments are read from the kernel argument segment by a pointer
     // that is opaque in each turn, so that nothing derived from them is held
@@ -408,6 +413,10 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
             }
         }
         if (valid && total > a.dose_cap + 1e-6) valid = 0;
+        if (TEAM && valid && nsteps > 1 && !s_team_ok) {   // a wait has run out: no exchange any more
+            if (a.live) atomicExch(&a.live[inst], (int)0x80000000);
+            valid = 0;
+        }
         if (!SLAB || TEAM) {
             s_valid = valid;
             s_nev = nev;
@@ -430,7 +439,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
     __syncthreads();
     if (!__builtin_amdgcn_readfirstlane(s_valid)) {
         if (!SLAB && tid == 0 && a.live) a.live[inst] = -1;   // slabs: set before the first step
-        continue;                                 // uniform across the workgroup (and its team)
+        continue;                                 // uniform across the workgroup
     }
     const int nev = __builtin_amdgcn_readfirstlane(s_nev);
     if constexpr (SLAB && !TEAM) {

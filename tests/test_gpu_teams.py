@@ -54,3 +54,38 @@ def test_waits_that_run_out_spoil_no_other_instance(gga, model_dict, L, n, spin_
         assert np.array_equal(lost, valid & (horizon >= 2))
     for a, b in zip(run(), ref):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("half_hour", [False, True])
+@pytest.mark.parametrize("L,variant,low", [(160, 18, 19), (160, 22, 19), (192, 20, 21), (192, 24, 21), (224, 16, 15), (256, 6, 5)])
+def test_tall_slabs_with_every_option(gga, model_dict, L, variant, low, half_hour):
+    """The tall team kernels with the oxygen effect, mitotic death and incomplete
+    repair, with fractions at hours or at half-hours, several instances per team:
+    bit for bit the results of slabs of 64 rows, one launch per step."""
+    print(f"tall slabs L={L} variant={variant} half_hour={half_hour}", flush=True)
+    md = copy.deepcopy(model_dict)
+    md.update(kappa=[4.0e-3, 2.0e-3, 2.0e-3], oer_max=3.0, oer_k=0.1, mitotic_death=1, repair_half_time=3.0, T_min=2)
+    n, K, H = 140, 4, 12
+    rng = np.random.default_rng(L + variant)
+    dose = rng.choice([1.0, 2.0, 3.0], (n, K)).astype(np.float32)
+    gap = rng.integers(1, 5, (n, K)).astype(np.int32) * (1 if half_hour else 2)
+    nfrac = rng.integers(0, K + 1, n).astype(np.int32)
+    nfrac[3] = K + 1                                           # refused
+    horizon = rng.integers(0, H + 1, n).astype(np.int32)
+    dd = _dev(dose, gap, nfrac)
+    cfg = gga.make_cfg(L, H, 1, seed=5, dose_cap=100.0, half_hour=half_hour)
+    lattice = np.full(n, L, np.int32)
+    out = []
+    try:
+        for v, teams in ((variant, True), (low, False)):
+            gga.set_variant(L, v)
+            gga.set_team_options(teams)
+            uneven = gga.simulate_uneven(md, cfg, *dd, lattice, horizon)
+            out.append([x.cpu().numpy() for x in (*uneven, *gga.simulate(md, cfg, *dd, traj=True))])
+    finally:
+        gga.set_team_options(True)
+        gga.clear_variant(L)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b, equal_nan=True)
+    final = out[0][2][np.arange(n) != 3]
+    assert len(np.unique(final)) > 10 and (final > 0).all()    # fractions, marks and divisions told on the counts

@@ -269,6 +269,9 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
     constexpr int RR = G::RR;
     constexpr int NWAVE = G::NWAVE;
     constexpr bool SLAB = G::SLAB;
+    // cells may be marked for mitotic death (teams load no state: without the
+    // option they never hold a mark)
+    constexpr bool MARKS = EXT || !TEAM;
     using Mask = typename G::Mask;
     using UMask = typename G::UMask;
 
@@ -1059,7 +1062,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                     if constexpr (EXT) doom_m[b] |= (UMask)((marked | (marked >> 15)) & 3u) << (j * UC + 2 * q);
                     if ((own_rows >> k) & 1u) live += __builtin_popcount(alive & ~nec);
                     // what lives keeps its mark, though only mitotic death reads it
-                    const uint32_t mark = w[q] & pk_sub(0u, alive & ~nec) & (DOOM_BIT * ONE);
+                    const uint32_t mark = MARKS ? w[q] & pk_sub(0u, alive & ~nec) & (DOOM_BIT * ONE) : 0u;
                     w[q] = bit_select(pk_sub(0u, alive), v, gone) | was | mark;
                 }
                 store_pairs(y, ux, w);
@@ -1156,7 +1159,7 @@ __global__ __launch_bounds__(64 * NW) void sim_kernel(SimArgs arg) {
                     }
                     // a winning parent keeps its mark (a daughter's site holds none)
                     w[q] &= ~(WAS_BIT * ONE);
-                    w[q] = bit_select(to, PROLIF * ONE | (w[q] & (DOOM_BIT * ONE)), w[q]);
+                    w[q] = bit_select(to, PROLIF * ONE | (MARKS ? w[q] & (DOOM_BIT * ONE) : 0u), w[q]);
                     any |= w[q];
                 }
                 store_pairs(y, ux, w);
